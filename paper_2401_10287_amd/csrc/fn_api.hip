@@ -324,8 +324,10 @@ fn_status make_plan(const Ctx &c, int64_t B, int op, Plan &p)
     per_walker += sizeof(items) / sizeof(items[0]) * 8;   // alignment slack
     int64_t bc = (int64_t)(CHUNK_BYTES / std::max<size_t>(per_walker, 1));
     if (bc < 64) bc = 64;
+    // forward-Laplacian chunks of whole rounds of the walking layer kernel
+    // (256 walkers in flight) where they hold one
     if (bc >= B) bc = B;
-    else bc = bc / 64 * 64;
+    else bc = p.fl && bc >= 256 ? bc / 256 * 256 : bc / 64 * 64;
     if (bc < 1) bc = 1;
     p.Bc = bc;
     for (Item &it : items) {
@@ -508,15 +510,17 @@ void forward_chunk(const Ctx &c, const Plan &p, const T *theta, const double *xw
             la.Hout = Hout; la.ldh_out = ldh;
             la.rows = b * s.N * TR; la.N = s.N; la.n3 = n3; la.w1 = s.w1; la.W1p = c.W.W1p;
             la.resid = l >= 1 ? 1 : 0;
+            la.nu = s.nu;
+            const bool walk = fl && walk_layer_supported(c.smode, la, TR, b);
             // the walker GEMM of layer l + 1 reads G before this kernel's
             // successor overwrites it, so G can take the next layer's means
-            if (l + 1 < s.L && stream_layer_whole_walkers(s.N, TR) && c.W.HWl[l + 1] == c.W.W1p) {
+            if (l + 1 < s.L && (walk || stream_layer_whole_walkers(s.N, TR)) && c.W.HWl[l + 1] == c.W.W1p) {
                 la.Gout = G;
-                la.nu = s.nu;
                 g_ready = true;
             }
             Timed t_(K_STREAM_GEMM, st);
-            launch_stream_layer(c.smode, la, TR, st);
+            if (walk) launch_walk_layer(c.smode, la, TR, b, st);
+            else launch_stream_layer(c.smode, la, TR, st);
         }
         if (!fused) {
             GemmArgs gx{};

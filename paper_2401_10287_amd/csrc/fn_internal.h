@@ -471,6 +471,11 @@ extern int g_det_stage;     // determinant kernels: envelope parameters staged i
 // FP32 pair layers on the matrix cores (false: vector kernel)
 extern bool g_pair_mfma;
 void launch_stream_layer(int mode, const LayerArgs &a, int TR, hipStream_t st);
+// The same layer, walker by walker, which also forms the next layer's spin
+// means (fn_walk.hip; bitwise the same results): B whole walkers of N
+// electrons.
+bool walk_layer_supported(int mode, const LayerArgs &a, int TR, int64_t B);
+void launch_walk_layer(int mode, const LayerArgs &a, int TR, int64_t B, hipStream_t st);
 
 // Every one-electron layer of a forward-Laplacian pass in one kernel
 // (fn_stack.hip), for two to four electrons (TR = 16) and w1 = 256.
