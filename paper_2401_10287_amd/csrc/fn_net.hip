@@ -7,6 +7,7 @@
 // maps act on all rows alike (they run as matrix products in fn_gemm.hip);
 // an element-wise f maps value a to f(a), tangent t to f'(a) t and Laplacian
 // l to f'(a) l + f''(a) sum_c t_c^2.
+#include "fn_env.h"
 #include "fn_internal.h"
 #include "fn_kernels.h"
 
@@ -819,50 +820,6 @@ __global__ __launch_bounds__(256) void k_layer_epi(const T *__restrict__ X, cons
 //   lap e = e (|grad q|^2 - lap q); lap(a e) = e lap a + a lap e + 2 grad a . grad e.
 // Output Phi[w][k][t][i][jj] (rows t = value, 3N tangents, Laplacian).
 // ---------------------------------------------------------------------------
-// One nucleus' term of orbital column col's envelope at electron position
-// xj: em = pi exp(-q) added to env, and with FL its contributions to the
-// electron's gradient and Laplacian of the envelope (all FP64).
-//   anisotropic: q = |Sigma d|, grad q = S d / q, S = Sigma^T Sigma,
-//                lap q = (tr S - |S d|^2 / q^2) / q;
-//   isotropic (Sigma = sigma I): q = |sigma| r with r = |d|,
-//                grad q = |sigma| d / r, |grad q|^2 = sigma^2, lap q = 2 |sigma| / r.
-template <typename T, bool FL>
-__device__ __forceinline__ void env_add(const Sys &s, const T *theta, int64_t piof, int64_t sigof, int col, int m,
-                                        const double *xj, double &env, double (&ge)[3], double &le)
-{
-    const double d[3] = {xj[0] - s.R[m][0], xj[1] - s.R[m][1], xj[2] - s.R[m][2]};
-    if (s.iso) {
-        const double sg = fabs((double)theta[sigof + (int64_t)col * s.M + m]);
-        const double r = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-        const double em = (double)theta[piof + (int64_t)col * s.M + m] * exp(-(sg * r));
-        env += em;
-        if constexpr (FL) {
-            const double gr = sg / r;
-            for (int a = 0; a < 3; ++a) ge[a] -= em * gr * d[a];
-            le += em * (sg * sg - 2.0 * gr);
-        }
-        return;
-    }
-    const T *Sgp = theta + sigof + ((int64_t)col * s.M + m) * 9;
-    double sd[3], ad[3], Sg[9];
-    for (int e = 0; e < 9; ++e) Sg[e] = (double)Sgp[e];
-    for (int p = 0; p < 3; ++p) sd[p] = Sg[3 * p] * d[0] + Sg[3 * p + 1] * d[1] + Sg[3 * p + 2] * d[2];
-    for (int a = 0; a < 3; ++a) ad[a] = Sg[a] * sd[0] + Sg[3 + a] * sd[1] + Sg[6 + a] * sd[2];
-    const double qd = sqrt(sd[0] * sd[0] + sd[1] * sd[1] + sd[2] * sd[2]);
-    const double em = (double)theta[piof + (int64_t)col * s.M + m] * exp(-qd);
-    env += em;
-    if constexpr (FL) {
-        double trS = 0.0;
-        for (int e = 0; e < 9; ++e) trS += Sg[e] * Sg[e];
-        const double iq = 1.0 / qd;
-        const double ad2 = ad[0] * ad[0] + ad[1] * ad[1] + ad[2] * ad[2];
-        const double lq = (trS - ad2 * iq * iq) * iq;
-        const double gq2 = ad2 * iq * iq;
-        for (int a = 0; a < 3; ++a) ge[a] -= em * ad[a] * iq;
-        le += em * (gq2 - lq);
-    }
-}
-
 template <typename T, bool FL>
 __global__ void k_envelope(Sys s, const double *x, const T *theta, int64_t gof, int64_t piof, int64_t sigof, int sp,
                            const T *O, int64_t ldo, int64_t B, int TR, double *Phi)
@@ -908,14 +865,6 @@ __global__ void k_envelope(Sys s, const double *x, const T *theta, int64_t gof, 
 //   lap log|det| = tr(A^-1 lap A) - sum_c tr(M_c M_c).
 // Record layout per (walker, spin, k): [sign, log|det|, grad[3N], lap].
 // ---------------------------------------------------------------------------
-template <typename T>
-__device__ inline T wave_sum(T v)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
 template <typename T, bool FL>
 __global__ __launch_bounds__(64) void k_det(const T *Phi, int64_t B, int K, int n, int TR, int n3, int sp,
                                             double *DR, int rec)
@@ -1031,7 +980,7 @@ __global__ __launch_bounds__(64) void k_det(const T *Phi, int64_t B, int K, int 
 // Envelope, entries, LU and traces in FP64 for every precision.
 // ---------------------------------------------------------------------------
 __host__ __device__ inline int orbdet_cd(int n) { return n >= 64 ? 1 : 64 / n; }
-constexpr int ORB_PF = 12;   // spins up to this size prefetch a direction's head values
+constexpr int ORB_PF = 12;   // spins up to this size keep a direction's column in registers
 
 size_t orbdet_lds(int n, bool fl)
 {
@@ -1047,8 +996,9 @@ __host__ __device__ inline size_t orbdet_stage_off(int n, bool fl)
 }
 
 // FL = false: value only (envelope, LU, sign and log|det|), LDS holds the matrix only.
-// REG: triangular solves of the directions in registers (spins of 7 ..
-// ORB_PF electrons, where LDS, not registers, bounds the resident waves)
+// REG: right-hand sides and triangular solves of the directions in registers
+// (forward-Laplacian form, spins of up to ORB_PF electrons).  Spins that the
+// direction-per-lane kernel of fn_det.hip does not take: 11 to 16 electrons.
 // Spins sp0 .. sp0 + nsp - 1 of equal size, B * K workgroups each.
 template <typename T, bool FL, bool REG, bool ST>
 __global__ __launch_bounds__(64) void k_orbdet(Sys s, const double *x, const T *theta, OrbSpins<T> S, int sp0,
@@ -1164,7 +1114,7 @@ __global__ __launch_bounds__(64) void k_orbdet(Sys s, const double *x, const T *
             const int mt = t0 + d, j = j0 + jj;
             const T *Oj = O + ((w * n + jj) * TR) * ldo + k * n;
             double *v = Mc + d * nn;
-            if (n <= ORB_PF) {
+            if constexpr (REG) {
                 // every row's head value is requested before the first is used
                 // (the stores below would otherwise order each load after the
                 // previous row's store)
@@ -1176,9 +1126,8 @@ __global__ __launch_bounds__(64) void k_orbdet(Sys s, const double *x, const T *
                 for (int r = 0; r < ORB_PF; ++r) pv[r] = perm[r < n ? r : n - 1];
 #pragma unroll
                 for (int r = 0; r < ORB_PF; ++r) ov[r] = (double)Oj[orow * ldo + pv[r]];
-                // REG: right-hand side and both triangular solves in registers
-                // (static indices), the solved column stored once; otherwise
-                // the right-hand side goes to LDS for the solves below
+                // right-hand side and both triangular solves in registers
+                // (static indices), the solved column stored once
                 double vv[ORB_PF];
 #pragma unroll
                 for (int r = 0; r < ORB_PF; ++r) {
@@ -1194,11 +1143,9 @@ __global__ __launch_bounds__(64) void k_orbdet(Sys s, const double *x, const T *
                             for (int a = 0; a < 3; ++a)
                                 dv += 2.0 * (double)Oj[(1 + 3 * j + a) * ldo + io] * GE[3 * e + a];
                         }
-                        if constexpr (REG) vv[r] = dv;
-                        else v[r * n + jj] = dv;
+                        vv[r] = dv;
                     }
                 }
-                if constexpr (REG) {
 #pragma unroll
                 for (int r = 1; r < ORB_PF; ++r) {
                     if (r < n) {
@@ -1221,7 +1168,6 @@ __global__ __launch_bounds__(64) void k_orbdet(Sys s, const double *x, const T *
 #pragma unroll
                 for (int r = 0; r < ORB_PF; ++r)
                     if (r < n) v[r * n + jj] = vv[r];
-                }
             } else {
                 for (int r = 0; r < n; ++r) {
                     const int io = perm[r], e = io * n + jj;
@@ -1235,8 +1181,6 @@ __global__ __launch_bounds__(64) void k_orbdet(Sys s, const double *x, const T *
                     }
                     v[r * n + jj] = dv;
                 }
-            }
-            if (!REG || n > ORB_PF) {
                 for (int r = 1; r < n; ++r) {
                     double acc = v[r * n + jj];
                     for (int c = 0; c < r; ++c) acc -= LU[r * n + c] * v[c * n + jj];
@@ -1962,6 +1906,7 @@ static void launch_orbdet_spins(const Sys &s, const double *x, const T *theta, c
         }
     }
 #undef FN_SMALL
+    if (launch_orbdet_lanes<T>(s, x, theta, S, sp0, nsp, n, B, TR, FL, DR, rec, st)) return;
     const dim3 g((unsigned)(nsp * B * s.K));
     // the determinant's envelope parameters staged in LDS when that adds at
     // most a quarter to the workgroup's LDS (more lowers the resident
@@ -1971,7 +1916,7 @@ static void launch_orbdet_spins(const Sys &s, const double *x, const T *theta, c
     const size_t staged = orbdet_stage_off(n, FL) + ((size_t)n * s.M * (s.iso ? 2 : 10) + n) * sizeof(T);
     const bool st_ok = g_det_stage && 4 * (staged - base) <= base && staged <= 64 * 1024;
     if constexpr (FL) {
-        if (n >= 7 && n <= ORB_PF) {
+        if (n <= ORB_PF) {
             if (st_ok)
                 hipLaunchKernelGGL((k_orbdet<T, true, true, true>), g, dim3(64), staged, st, s, x, theta, S, sp0,
                                    B, TR, DR, rec);
