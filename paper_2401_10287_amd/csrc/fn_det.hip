@@ -208,7 +208,7 @@ __global__ __launch_bounds__(64 * DET_WAVES) void k_orbdet_lanes(Sys s, const do
         }
         typedef DetRow<T, NS> H;
         constexpr int V = H::V, NL = H::NL, RS = H::RS, CW = NS == 1 ? 1 : 2;
-        struct alignas(sizeof(T) * V) vec { T x[V]; };
+        typedef T vec __attribute__((ext_vector_type(V)));
         T *row = (T *)(smem_raw + (size_t)nprm * sizeof(T) + wave * det_wave_bytes<T, NS, FL>() + (5 * NN * 8 + 15) / 16 * 16);
         const T *Ow = O + w * NS * TR * ldo + k * NS;
         const int64_t estep = (int64_t)TR * ldo;
@@ -250,7 +250,7 @@ __global__ __launch_bounds__(64 * DET_WAVES) void k_orbdet_lanes(Sys s, const do
 #pragma unroll
                         for (int z = 0; z < V; ++z) {
                             const int i = V * l + z;
-                            D[y][i] = EV[c * NS + i] * (double)o.x[z];
+                            D[y][i] = EV[c * NS + i] * (double)o[z];
                         }
                     }
                     if (own)

@@ -22,7 +22,7 @@
 //               the exact hi + mid + lo split of the FP32 activations: three
 //               products, each exact, accumulated in FP32
 //   GEMM_BF16W2 BF16 weights times the hi + lo split of the activations
-//   GEMM_F64    FP64 on the vector ALUs (64 x 64 tiles)
+//   GEMM_F64    v_mfma_f64_16x16x4_f64, FP64 operands (64 x 64 tiles, 16 x 16 for small grids)
 #include "fn_internal.h"
 
 namespace fn {
@@ -375,64 +375,167 @@ __global__ __launch_bounds__(256) void k_gemm_splitk2(GemmArgs a0, GemmArgs a1, 
     else gemm_splitk_tile<MODE>(a1, (int64_t)blockIdx.x - nb0);
 }
 
-// FP64 on the vector ALUs: 64 x 64 tiles, 16-step reduction tiles, 4 x 4
-// outputs per thread.
-__global__ __launch_bounds__(256) void k_gemm_f64(GemmArgs a)
+// FP64 on the matrix cores (v_mfma_f64_16x16x4_f64, accumulator element e at
+// row 4 e + lane / 16, column lane % 16).  Reduction index of an operand
+// fragment: lane group g = lane / 16 holds the pair 2 g, 2 g + 1 of eight
+// consecutive indices, so that one 16-byte load serves two instructions (the
+// order of the sum is that of the pairs).
+//
+// Tiled kernel: bound by the matrix cores.  128 x BN tiles (BN = 64, 128), each
+// wave 64 rows x BN / 2 columns; reduction tiles of 16 through LDS, double
+// buffered (rows padded to 18: a fragment's reads fall on distinct banks), the
+// next tile's loads issued before the current tile's products; the two column
+// tiles of a row block run one after the other on one XCD.  1024 walkers, 4
+// electrons, the ten products of a local energy (57344 rows x 320 x 256 the
+// largest): 64 x 64 tiles with 4 x 4 outputs per thread on the vector ALUs 2.57
+// ms, 64 x 64 tiles on the matrix cores 1.92 ms, here 0.99 ms.
+constexpr int DBK = 16, DLS = DBK + 2;
+typedef __attribute__((__vector_size__(4 * sizeof(double)))) double f64x4;
+typedef __attribute__((__vector_size__(2 * sizeof(double)))) double f64x2;
+
+template <int BN>
+__global__ __launch_bounds__(256, 2) void k_gemm_f64(GemmArgs a)
 {
-    __shared__ double sA[16][64 + 1];
-    __shared__ double sB[16][64 + 1];
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const int64_t m0 = (int64_t)blockIdx.x * 64;
-    const int n0 = blockIdx.y * 64;
-    const double *A1 = (const double *)a.A1, *A2 = (const double *)a.A2, *W = (const double *)a.W;
-    int64_t arow[4];
-    bool aval[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        int f = tid + 256 * v;
-        int64_t r = m0 + (f >> 4);
-        aval[v] = r < a.rows;
-        arow[v] = gemm_a_row(a, r);
+    constexpr int WJ = BN / 32, VA = 4, VB = BN / 32;
+    __shared__ __attribute__((aligned(16))) double sA[2][128 * DLS];
+    __shared__ __attribute__((aligned(16))) double sB[2][BN * DLS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int ncb = (a.nout + BN - 1) / BN;
+    int64_t rb;
+    int cb;
+    if (ncb <= 2) {
+        xcd_tile(blockIdx.x, ncb, rb, cb);
+    } else {
+        rb = blockIdx.x / ncb;
+        cb = (int)(blockIdx.x % ncb);
     }
-    double acc[4][4] = {};
-    const int K = a.K1 + a.K2;
-    for (int kb = 0; kb < K; kb += 16) {
+    const int64_t m0 = rb * 128;
+    const int n0 = cb * BN;
+    if (m0 >= a.rows) return;
+    const int qm = (wave >> 1) * 64, qn = (wave & 1) * (BN / 2);
+    // this thread's pairs of each operand tile: row tid / 8 + 32 v, indices 2 (tid % 8) ..; rows
+    // past the end repeat the first one (their outputs are not stored)
+    const int lr = tid >> 3, lk = 2 * (tid & 7);
+    const double *pa1[VA], *pa2[VA], *pw[VB];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            int f = tid + 256 * v;
-            int r = f >> 4, kk = f & 15, k = kb + kk;
-            double x = 0.0;
-            if (aval[v]) x = k < a.K1 ? A1[arow[v] * a.lda1 + k] : A2[arow[v] * a.lda2 + (k - a.K1)];
-            sA[kk][r] = x;
-            int o = n0 + r;
-            sB[kk][r] = o < a.nout ? W[(int64_t)o * a.ldw + k] : 0.0;
-        }
+    for (int v = 0; v < VA; ++v) {
+        const int64_t r = m0 + lr + 32 * v;
+        const int64_t ar = gemm_a_row(a, r < a.rows ? r : m0);
+        pa1[v] = (const double *)a.A1 + ar * a.lda1 + lk;
+        pa2[v] = (const double *)a.A2 + ar * a.lda2 + lk - a.K1;
+    }
+#pragma unroll
+    for (int v = 0; v < VB; ++v) {
+        const int o = n0 + lr + 32 * v;
+        pw[v] = (const double *)a.W + (int64_t)(o < a.nout ? o : n0) * a.ldw + lk;
+    }
+    const int nk = (a.K1 + a.K2) / DBK;
+    f64x2 xa[VA], xw[VB];
+    auto load = [&](int kt) {
+        const int kb = kt * DBK;               // a tile lies in one operand part (K1 is a multiple of 16)
+#pragma unroll
+        for (int v = 0; v < VA; ++v) xa[v] = *(const f64x2 *)((kb < a.K1 ? pa1[v] : pa2[v]) + kb);
+#pragma unroll
+        for (int v = 0; v < VB; ++v) xw[v] = *(const f64x2 *)(pw[v] + kb);
+    };
+    auto store = [&](int buf) {
+#pragma unroll
+        for (int v = 0; v < VA; ++v) *(f64x2 *)&sA[buf][(lr + 32 * v) * DLS + lk] = xa[v];
+#pragma unroll
+        for (int v = 0; v < VB; ++v) *(f64x2 *)&sB[buf][(lr + 32 * v) * DLS + lk] = xw[v];
+    };
+    f64x4 acc[4][WJ];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < WJ; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
+    const int fr = lane & 15, fk = 2 * (lane >> 4);
+    if (nk > 0) {
+        load(0);
+        store(0);
+    }
+    for (int kt = 0; kt < nk; ++kt) {
+        if (kt + 1 < nk) load(kt + 1);
         __syncthreads();
+        const double *A = sA[kt & 1] + (qm + fr) * DLS + fk, *B = sB[kt & 1] + (qn + fr) * DLS + fk;
 #pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            double av[4], bv[4];
+        for (int h = 0; h < DBK / 8; ++h) {
+            f64x2 fa[4], fb[WJ];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) av[i] = sA[kk][ty * 4 + i];
+            for (int i = 0; i < 4; ++i) fa[i] = *(const f64x2 *)(A + 16 * i * DLS + 8 * h);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) bv[j] = sB[kk][tx * 4 + j];
+            for (int j = 0; j < WJ; ++j) fb[j] = *(const f64x2 *)(B + 16 * j * DLS + 8 * h);
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fma(av[i], bv[j], acc[i][j]);
+                for (int j = 0; j < WJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[i][0], fb[j][0], acc[i][j], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < WJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[i][1], fb[j][1], acc[i][j], 0, 0, 0);
         }
-        __syncthreads();
+        if (kt + 1 < nk) store((kt + 1) & 1);
     }
     double *C = (double *)a.C;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        int64_t row = m0 + ty * 4 + i;
-        if (row >= a.rows) continue;
-        if (a.c_rows_per_group > 0) row = remap_row(row, a.c_rows_per_group, a.c_group_stride, a.c_row_offset);
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            int col = n0 + tx * 4 + j;
-            if (col < a.nout) C[row * a.ldc + col] = acc[i][j];
+        for (int e = 0; e < 4; ++e) {
+            int64_t row = m0 + qm + 16 * i + 4 * e + (lane >> 4);
+            if (row >= a.rows) continue;
+            if (a.c_rows_per_group > 0) row = remap_row(row, a.c_rows_per_group, a.c_group_stride, a.c_row_offset);
+#pragma unroll
+            for (int j = 0; j < WJ; ++j) {
+                const int col = n0 + qn + 16 * j + (lane & 15);
+                if (col < a.nout) C[row * a.ldc + col] = acc[i][j][e];
+            }
         }
+}
+
+// Grids of fewer 128 x 64 tiles than CUs: bound by the latency of one tile.  A
+// wave takes a 16 x 16 tile with its fragments straight from memory, 32
+// reduction indices (four pairs of each operand per lane) requested ahead.
+// 512 rows x 64 x 32: 14 us on the tiled vector kernel, 5 us here.
+__global__ __launch_bounds__(64) void k_gemm_f64_small(GemmArgs a)
+{
+    const int lane = threadIdx.x, fr = lane & 15, fk = 2 * (lane >> 4);
+    const int64_t m0 = (int64_t)blockIdx.x * 16;
+    const int n0 = blockIdx.y * 16;
+    const int64_t ar = gemm_a_row(a, m0 + fr < a.rows ? m0 + fr : m0);
+    const double *pa1 = (const double *)a.A1 + ar * a.lda1 + fk, *pa2 = (const double *)a.A2 + ar * a.lda2 + fk - a.K1;
+    const double *pw = (const double *)a.W + (int64_t)(n0 + fr < a.nout ? n0 + fr : n0) * a.ldw + fk;
+    const int K = a.K1 + a.K2;
+    f64x2 xa[4], xw[4];
+    auto load = [&](int kb) {
+        const double *p = (kb < a.K1 ? pa1 : pa2) + kb;       // (K1 is a multiple of 32)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            xa[v] = *(const f64x2 *)(p + 8 * v);
+            xw[v] = *(const f64x2 *)(pw + kb + 8 * v);
+        }
+    };
+    // two chains of sums, added at the end
+    f64x4 c0 = {0.0, 0.0, 0.0, 0.0}, c1 = {0.0, 0.0, 0.0, 0.0};
+    if (K > 0) load(0);
+    for (int kb = 0; kb < K; kb += 32) {
+        f64x2 fa[4], fw[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) { fa[v] = xa[v]; fw[v] = xw[v]; }
+        if (kb + 32 < K) load(kb + 32);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            c0 = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[v][0], fw[v][0], c0, 0, 0, 0);
+            c1 = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[v][1], fw[v][1], c1, 0, 0, 0);
+        }
+    }
+    double *C = (double *)a.C;
+    const int col = n0 + fr;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        int64_t row = m0 + 4 * e + (lane >> 4);
+        if (row >= a.rows || col >= a.nout) continue;
+        if (a.c_rows_per_group > 0) row = remap_row(row, a.c_rows_per_group, a.c_group_stride, a.c_row_offset);
+        C[row * a.ldc + col] = c0[e] + c1[e];
     }
 }
 
@@ -524,8 +627,19 @@ hipError_t launch_gemm(int mode, const GemmArgs &a, hipStream_t st)
 {
     if (a.rows <= 0 || a.nout <= 0) return hipSuccess;
     if (mode == GEMM_F64) {
-        dim3 grid((unsigned)((a.rows + 63) / 64), (unsigned)((a.nout + 63) / 64));
-        hipLaunchKernelGGL(k_gemm_f64, grid, dim3(256), 0, st, a);
+        // reduction parts are multiples of 32 by construction (padded widths)
+        const int64_t nrb = (a.rows + 127) / 128;
+        auto tiled = [&](auto bn) {
+            constexpr int BN = decltype(bn)::value;
+            const int ncb = (a.nout + BN - 1) / BN;
+            const int64_t blocks = ncb <= 2 ? xcd_grid(nrb, ncb) : nrb * ncb;
+            hipLaunchKernelGGL((k_gemm_f64<BN>), dim3((unsigned)blocks), dim3(256), 0, st, a);
+        };
+        if (nrb * ((a.nout + 63) / 64) < 256)
+            hipLaunchKernelGGL(k_gemm_f64_small, dim3((unsigned)((a.rows + 15) / 16), (unsigned)((a.nout + 15) / 16)), dim3(64),
+                               0, st, a);
+        else if (a.nout <= 64 || nrb * ((a.nout + 127) / 128) < 256) tiled(std::integral_constant<int, 64>{});
+        else tiled(std::integral_constant<int, 128>{});
     } else {
         launch_mfma(mode, a, nullptr, st);
     }
