@@ -672,7 +672,7 @@ void backward_chunk(const Ctx &c, const Plan &p, const T *theta, const double *x
         launch_colsum<T>(EP, (int64_t)kn * s.M * env_partials(s), kn * s.M * env_partials(s), b, part, gacc, c.P.pi[sp],
                          env_partials(s), c.P.sig[sp], st);
         launch_colsum<T>(Ga, KNp, kn, b * n, part, gacc, c.P.g[sp], 0, 0, st);
-        launch_tn<T>((const T *)(ws + p.H[s.L]), ldh, w1, Ga, KNp, kn, b * n, n, N, j0, part, gacc, c.P.w[sp], kn, st);
+        launch_tn<T>((const T *)(ws + p.H[s.L]), ldh, w1, Ga, KNp, kn, b * n, n, N, j0, part, p.part_elems, gacc, c.P.w[sp], kn, st);
         GemmArgs g{};
         g.A1 = Ga; g.lda1 = KNp; g.K1 = KNp;
         g.W = ws + p.wb[sp]; g.ldw = KNp;
@@ -695,12 +695,17 @@ void backward_chunk(const Ctx &c, const Plan &p, const T *theta, const double *x
         const T *Vl = p.vround ? (const T *)(ws + p.vr[l]) : theta + voff;
         launch_bwd_gz<T>(Gy, Tl, b, N, w1, Gz, SGz, st);
         launch_colsum<T>(Gz, w1, w1, rows, part, gacc, c.P.b[l], 0, 0, st);
-        launch_tn<T>(Hl, ldh, dh, Gz, w1, w1, rows, 0, 0, 0, part, gacc, voff, w1, st);
+        launch_tn<T>(Hl, ldh, dh, Gz, w1, w1, rows, 0, 0, 0, part, p.part_elems, gacc, voff, w1, st);
         const T *GIl = (const T *)(ws + p.GI) + (int64_t)l * p.gi_layer_stride;
-        launch_tn<T>(GIl, ldg, 2 * dp, Gz, w1, w1, rows, 0, 0, 0, part, gacc, voff + (int64_t)3 * dh * w1, w1, st);
+        launch_tn<T>(GIl, ldg, 2 * dp, Gz, w1, w1, rows, 0, 0, 0, part, p.part_elems, gacc, voff + (int64_t)3 * dh * w1, w1, st);
         launch_spin_mean<T>(Hl, ldh, b, N, s.nu, 1, dh, HWl, G, st);
-        launch_tn<T>(G, 2 * HWl, dh, SGz, w1, w1, b, 0, 0, 0, part, gacc, voff + (int64_t)dh * w1, w1, st);
-        launch_tn<T>(G + HWl, 2 * HWl, dh, SGz, w1, w1, b, 0, 0, 0, part, gacc, voff + (int64_t)2 * dh * w1, w1, st);
+        // V_up and V_dn: one product where the two means' columns are adjacent
+        if (HWl == dh) {
+            launch_tn<T>(G, 2 * HWl, 2 * dh, SGz, w1, w1, b, 0, 0, 0, part, p.part_elems, gacc, voff + (int64_t)dh * w1, w1, st);
+        } else {
+            launch_tn<T>(G, 2 * HWl, dh, SGz, w1, w1, b, 0, 0, 0, part, p.part_elems, gacc, voff + (int64_t)dh * w1, w1, st);
+            launch_tn<T>(G + HWl, 2 * HWl, dh, SGz, w1, w1, b, 0, 0, 0, part, p.part_elems, gacc, voff + (int64_t)2 * dh * w1, w1, st);
+        }
         // adjoints of the pair means (to the pair stream) and of h^l
         GemmArgs gq{};
         gq.A1 = Gz; gq.lda1 = w1; gq.K1 = w1;

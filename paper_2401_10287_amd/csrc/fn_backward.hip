@@ -15,6 +15,7 @@
 // Weight gradients are sums over walkers x electrons of outer products; they
 // are formed as split row reductions whose partial sums are added in a fixed
 // order, so the result does not depend on scheduling.
+#include <algorithm>
 #include <type_traits>
 
 #include "fn_internal.h"
@@ -678,136 +679,110 @@ __global__ __launch_bounds__(256) void k_pair_backward_mfma(Sys s, const double 
     }
 }
 
-// ---------------------------------------------------------------------------
-// weight-gradient products C[a][b] = sum_r X[r][a] Y[r][b] (split over rows)
-// partial[s][a][b] for row range s; X rows may be remapped by groups.
-// ---------------------------------------------------------------------------
+// part[s][a][b] = sum over the rows r of split s of X[xr(r)][a] Y[r][b] (xr: the
+// row map of one spin's electrons when per > 0), on the matrix cores.
+//
+// What bounds it: the FP32 (FP64) matrix cores.  A lane loads 16 bytes of a row:
+// V = 4 (2) consecutive columns, column V m + i of which is row m of fragment
+// i, so one load of each operand feeds V x V instructions of a 16 V x 16 V tile
+// per wave, four rows at a time, straight from memory (no LDS, no barriers),
+// TN_PF such steps requested ahead.  The four waves of a workgroup take
+// consecutive parts of the split's rows and are added in wave order; all tiles
+// of a split follow each other on one XCD, so its rows come from HBM once.
+// (A workgroup per 64 x 64 tile with 64 rows staged in LDS per barrier: 12
+// electrons, 4096 walkers, the gradient's 18 products 855 -> 590 us; FP64, 2
+// electrons, 256 walkers, ten products 722 -> 58 us.)
+typedef __attribute__((__vector_size__(4 * sizeof(double)))) double f64x4;
 template <typename T>
-__global__ __launch_bounds__(256) void k_tn_partial(const T *X, int64_t ldx, int NA, const T *Y, int64_t ldy, int NB,
-                                                    int64_t R, int64_t per, int64_t stride, int64_t off,
-                                                    int64_t rows_per_split, T *part)
-{
-    __shared__ T sx[16][64 + 1];
-    __shared__ T sy[16][64 + 1];
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const int a0 = blockIdx.x * 64, b0 = blockIdx.y * 64;
-    const int64_t r0 = (int64_t)blockIdx.z * rows_per_split;
-    const int64_t r1 = r0 + rows_per_split < R ? r0 + rows_per_split : R;
-    T acc[4][4] = {};
-    for (int64_t rb = r0; rb < r1; rb += 16) {
-        for (int q = tid; q < 16 * 64; q += 256) {
-            const int rr = q / 64, c = q % 64;
-            const int64_t r = rb + rr;
-            T vx = T(0), vy = T(0);
-            if (r < r1) {
-                const int64_t xr = per > 0 ? remap_row(r, per, stride, off) : r;
-                if (a0 + c < NA) vx = X[xr * ldx + a0 + c];
-                if (b0 + c < NB) vy = Y[r * ldy + b0 + c];
-            }
-            sx[rr][c] = vx;
-            sy[rr][c] = vy;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int rr = 0; rr < 16; ++rr) {
-            T xa[4], yb[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) { xa[u] = sx[rr][ty * 4 + u]; yb[u] = sy[rr][tx * 4 + u]; }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) acc[u][v] += xa[u] * yb[v];
-        }
-        __syncthreads();
-    }
-    T *p = part + (int64_t)blockIdx.z * NA * NB;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int a = a0 + ty * 4 + u;
-        if (a >= NA) continue;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int b = b0 + tx * 4 + v;
-            if (b < NB) p[(int64_t)a * NB + b] = acc[u][v];
-        }
-    }
-}
+struct TnTile {
+    static constexpr int V = 16 / (int)sizeof(T), W = 16 * V;
+    typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+    typedef typename std::conditional<sizeof(T) == 4, f32x4, f64x4>::type acc;
+};
+__device__ __forceinline__ f32x4 tn_mfma(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+__device__ __forceinline__ f64x4 tn_mfma(double a, double b, f64x4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+constexpr int TN_PF = 4;
 
-// FP32 on the matrix cores: the same 64 x 64 output tile, each wave a
-// 32 x 32 quadrant (2 x 2 accumulators of v_mfma_f32_16x16x4f32, rows as the
-// reduction dimension), rows staged 64 at a time; X^T and Y are both read
-// straight from the row-major LDS tiles (lane: column lane & 15, row lane >> 4).
-template <>
-__global__ __launch_bounds__(256) void k_tn_partial<float>(const float *X, int64_t ldx, int NA, const float *Y,
-                                                          int64_t ldy, int NB, int64_t R, int64_t per,
-                                                          int64_t stride, int64_t off, int64_t rows_per_split,
-                                                          float *part)
+template <typename T>
+__global__ __launch_bounds__(256) void k_tn_partial(const T *__restrict__ X, int64_t ldx, int NA, const T *__restrict__ Y,
+                                                    int64_t ldy, int NB, int64_t R, int64_t per, int64_t stride,
+                                                    int64_t off, int64_t rows_per_split, int S, T *__restrict__ part)
 {
-    constexpr int RC = 64, LS = 64 + 4;
-    __shared__ float sx[RC][LS];
-    __shared__ float sy[RC][LS];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int a0 = blockIdx.x * 64, b0 = blockIdx.y * 64;
-    const int qa = (wave >> 1) * 32, qb = (wave & 1) * 32;
-    const int64_t r0 = (int64_t)blockIdx.z * rows_per_split;
-    const int64_t r1 = r0 + rows_per_split < R ? r0 + rows_per_split : R;
-    f32x4 acc[2][2];
+    typedef TnTile<T> H;
+    typedef typename H::vec vec;
+    typedef typename H::acc accv;
+    constexpr int V = H::V, W = H::W, PF = TN_PF;
+    __shared__ accv red[3][V][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nta = (NA + W - 1) / W, tiles = nta * ((NB + W - 1) / W);
+    const int idx = (int)(blockIdx.x >> 3), sp = (idx / tiles) * 8 + (int)(blockIdx.x & 7), tile = idx % tiles;
+    if (sp >= S) return;
+    const int a0 = (tile % nta) * W, b0 = (tile / nta) * W;
+    const int64_t s0 = (int64_t)sp * rows_per_split, s1 = s0 + rows_per_split < R ? s0 + rows_per_split : R;
+    const int64_t rw = (rows_per_split + 3) / 4;               // rows of a wave
+    const int64_t r0 = s0 + wave * rw, r1 = r0 + rw < s1 ? r0 + rw : s1;
+    const int m = lane & 15, g = lane >> 4;
+    // columns past the end read column 0 (their outputs are not stored)
+    const T *xc = X + (a0 + V * m < NA ? a0 + V * m : 0), *yc = Y + (b0 + V * m < NB ? b0 + V * m : 0);
+    accv acc[V][V];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < V; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // a thread keeps column tid & 63 and rows tid / 64 + 4 u of a stage; all
-    // of its loads are issued before the first store to LDS
-    const int c = tid & 63, rq = tid >> 6;
-    const bool cx = a0 + c < NA, cy = b0 + c < NB;
-    for (int64_t rb = r0; rb < r1; rb += RC) {
-        float vx[RC / 4], vy[RC / 4];
+        for (int j = 0; j < V; ++j) acc[i][j] = accv{T(0), T(0), T(0), T(0)};
+    vec xv[PF], yv[PF];
+    auto load = [&](int64_t rb) {
 #pragma unroll
-        for (int u = 0; u < RC / 4; ++u) {
-            const int64_t r = rb + rq + 4 * u;
-            vx[u] = 0.f;
-            vy[u] = 0.f;
-            if (r < r1) {
-                const int64_t xr = per > 0 ? remap_row(r, per, stride, off) : r;
-                if (cx) vx[u] = X[xr * ldx + a0 + c];
-                if (cy) vy[u] = Y[r * ldy + b0 + c];
+        for (int u = 0; u < PF; ++u) {
+            const int64_t r = rb + 4 * u + g;
+            const int64_t rc = r < r1 ? r : r1 - 1;
+            const int64_t xr = per > 0 ? remap_row(rc, per, stride, off) : rc;
+            vec x = *(const vec *)(xc + xr * ldx), y = *(const vec *)(yc + rc * ldy);
+            if (r >= r1) {
+                x = vec(T(0));
+                y = vec(T(0));
             }
+            xv[u] = x;
+            yv[u] = y;
         }
+    };
+    if (r0 < r1) load(r0);
+    for (int64_t rb = r0; rb < r1; rb += 4 * PF) {
+        vec x[PF], y[PF];
 #pragma unroll
-        for (int u = 0; u < RC / 4; ++u) {
-            sx[rq + 4 * u][c] = vx[u];
-            sy[rq + 4 * u][c] = vy[u];
+        for (int u = 0; u < PF; ++u) {
+            x[u] = xv[u];
+            y[u] = yv[u];
         }
-        __syncthreads();
-#pragma unroll 4
-        for (int kk = 0; kk < RC / 4; ++kk) {
-            const int rr = 4 * kk + (lane >> 4);
-            float fa[2], fb[2];
+        if (rb + 4 * PF < r1) load(rb + 4 * PF);
 #pragma unroll
-            for (int i = 0; i < 2; ++i) fa[i] = sx[rr][qa + 16 * i + (lane & 15)];
+        for (int u = 0; u < PF; ++u)
 #pragma unroll
-            for (int j = 0; j < 2; ++j) fb[j] = sy[rr][qb + 16 * j + (lane & 15)];
+            for (int i = 0; i < V; ++i)
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i], fb[j], acc[i][j], 0, 0, 0);
-        }
-        __syncthreads();
+                for (int j = 0; j < V; ++j) acc[i][j] = tn_mfma(x[u][i], y[u][j], acc[i][j]);
     }
-    // accumulator (i, j) element e: a = qa + 16 i + 4 (lane >> 4) + e, b = qb + 16 j + (lane & 15)
-    float *p = part + (int64_t)blockIdx.z * NA * NB;
+    // element e of block (i, j): row m' = 4 g + e (FP32) or 4 e + g (FP64), column lane % 16
+    T *p = part + (int64_t)sp * NA * NB;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < V; ++i) {
+        __syncthreads();
+        if (wave > 0)
+#pragma unroll
+            for (int j = 0; j < V; ++j) red[wave - 1][j][lane] = acc[i][j];
+        __syncthreads();
+        if (wave > 0) continue;
+#pragma unroll
+        for (int j = 0; j < V; ++j) acc[i][j] = ((acc[i][j] + red[0][j][lane]) + red[1][j][lane]) + red[2][j][lane];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int a = a0 + qa + 16 * i + 4 * (lane >> 4) + e;
+            const int a = a0 + V * (sizeof(T) == 4 ? 4 * g + e : 4 * e + g) + i;
             if (a >= NA) continue;
+            T *q = p + (int64_t)a * NB + b0 + V * m;
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int b = b0 + qb + 16 * j + (lane & 15);
-                if (b < NB) p[(int64_t)a * NB + b] = acc[i][j][e];
-            }
+            for (int j = 0; j < V; ++j)
+                if (b0 + V * m + j < NB) q[j] = acc[i][j][e];
         }
+    }
 }
 
 // acc[dst(a, b)] += sum_s part[s][a][b]; dst = off + a * lda_out + b
@@ -817,6 +792,7 @@ __global__ void k_tn_reduce(const T *part, int S, int NA, int NB, double *acc, i
     const int64_t n = (int64_t)NA * NB;
     for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < n; q += (int64_t)gridDim.x * blockDim.x) {
         double v = 0.0;
+#pragma unroll 8
         for (int s = 0; s < S; ++s) v += (double)part[(int64_t)s * n + q];
         const int a = (int)(q / NB), b = (int)(q % NB);
         acc[off + (int64_t)a * lda_out + b] += v;
@@ -852,6 +828,7 @@ __global__ void k_colsum_reduce(const T *part, int S, int C, double *acc, int64_
 {
     for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < C; c += gridDim.x * blockDim.x) {
         double v = 0.0;
+#pragma unroll 16
         for (int s = 0; s < S; ++s) v += (double)part[(int64_t)s * C + c];
         if (!env_map) {
             acc[off + c] += v;
@@ -1055,14 +1032,20 @@ int tn_splits(int64_t R)
 
 template <typename T>
 void launch_tn(const T *X, int64_t ldx, int NA, const T *Y, int64_t ldy, int NB, int64_t R, int64_t per,
-               int64_t stride, int64_t off, T *part, double *acc, int64_t acc_off, int64_t lda_out, hipStream_t st)
+               int64_t stride, int64_t off, T *part, int64_t part_elems, double *acc, int64_t acc_off, int64_t lda_out,
+               hipStream_t st)
 {
     if (R <= 0 || NA <= 0 || NB <= 0) return;
-    const int S = tn_splits(R);
+    constexpr int W = TnTile<T>::W;
+    const int tiles = ((NA + W - 1) / W) * ((NB + W - 1) / W);
+    // three workgroups per CU where the rows give them, 32 rows per wave or more
+    int64_t S = std::min<int64_t>(std::min<int64_t>(768 / tiles + 1, max_splits()), R / 128);
+    S = std::min<int64_t>(S, part_elems / ((int64_t)NA * NB));       // the partials' buffer
+    if (S < 1) S = 1;
     const int64_t rps = (R + S - 1) / S;
-    dim3 g((unsigned)((NA + 63) / 64), (unsigned)((NB + 63) / 64), (unsigned)S);
-    hipLaunchKernelGGL(k_tn_partial<T>, g, dim3(256), 0, st, X, ldx, NA, Y, ldy, NB, R, per, stride, off, rps, part);
-    hipLaunchKernelGGL(k_tn_reduce<T>, dim3(gridn((int64_t)NA * NB)), dim3(256), 0, st, part, S, NA, NB, acc, acc_off,
+    hipLaunchKernelGGL(k_tn_partial<T>, dim3((unsigned)((S + 7) / 8 * 8 * tiles)), dim3(256), 0, st, X, ldx, NA, Y, ldy, NB,
+                       R, per, stride, off, rps, (int)S, part);
+    hipLaunchKernelGGL(k_tn_reduce<T>, dim3(gridn((int64_t)NA * NB)), dim3(256), 0, st, part, (int)S, NA, NB, acc, acc_off,
                        lda_out);
 }
 
@@ -1107,7 +1090,7 @@ void launch_pack_head_bwd(const T *theta, int64_t woff, int w1, int kn, int KNp,
     template int64_t launch_pair_backward<T>(const Sys &, const double *, const T *, const ParamLayout &, int64_t,    \
                                              const T *, int64_t, int64_t, const float *, T *, int64_t, hipStream_t);  \
     template void launch_tn<T>(const T *, int64_t, int, const T *, int64_t, int, int64_t, int64_t, int64_t, int64_t,  \
-                               T *, double *, int64_t, int64_t, hipStream_t);                                         \
+                               T *, int64_t, double *, int64_t, int64_t, hipStream_t);                                         \
     template void launch_colsum<T>(const T *, int64_t, int, int64_t, T *, double *, int64_t, int, int64_t,           \
                                    hipStream_t);                                                                      \
     template void launch_grad_out<T>(const double *, int64_t, T *, hipStream_t);                                      \

@@ -137,7 +137,8 @@ int64_t launch_pair_backward(const Sys &s, const double *x, const T *theta, cons
 int max_splits();
 template <typename T>
 void launch_tn(const T *X, int64_t ldx, int NA, const T *Y, int64_t ldy, int NB, int64_t R, int64_t per,
-               int64_t stride, int64_t off, T *part, double *acc, int64_t acc_off, int64_t lda_out, hipStream_t st);
+               int64_t stride, int64_t off, T *part, int64_t part_elems, double *acc, int64_t acc_off, int64_t lda_out,
+               hipStream_t st);
 template <typename T>
 void launch_colsum(const T *in, int64_t ld, int C, int64_t R, T *part, double *acc, int64_t off, int env_map,
                    int64_t off2, hipStream_t st);
