@@ -763,6 +763,13 @@ template <typename T>
 fn_status run_forward(const Ctx &c, const Plan &p, const void *theta, const double *x, int64_t B, double *log_abs,
                       int8_t *sign, double *e_loc, double *parts, void *ws, hipStream_t st)
 {
+    if constexpr (std::is_same<T, double>::value)
+        if (!e_loc && small_walk_supported(c.s, c.P, B)) {
+            Timed t_(K_STREAM_GEMM, st);
+            launch_small_walk(c.s, c.P, (const double *)theta, const_cast<double *>(x), log_abs, sign, B, 0, 0.0,
+                              GroupTable{}, nullptr, nullptr, nullptr, st);
+            return hip_status();
+        }
     pack_weights<T>(c, p, (const T *)theta, (char *)ws, st);
     forward<T>(c, p, (const T *)theta, x, B, log_abs, sign, e_loc, parts, (char *)ws, st);
     return hip_status();
@@ -775,6 +782,19 @@ fn_status run_metropolis(const Ctx &c, const Plan &p, const void *theta, double 
 {
     char *w = (char *)ws;
     const int n3 = 3 * c.s.N;
+    if constexpr (std::is_same<T, double>::value)
+        if (small_walk_supported(c.s, c.P, B)) {
+            GroupTable g{};
+            g.n = 1;
+            g.w0[1] = B;
+            g.k0[0] = (uint32_t)seed;
+            g.k1[0] = (uint32_t)(seed >> 32);
+            g.step[0] = (uint32_t)step0;
+            g.stream[0] = stream_id;
+            Timed t_(K_STREAM_GEMM, st);
+            launch_small_walk(c.s, c.P, (const double *)theta, x, log_abs, nullptr, B, n_steps, sigma, g, z, u, n_accept, st);
+            return hip_status();
+        }
     pack_weights<T>(c, p, (const T *)theta, w, st);
     double *xp = (double *)(w + p.xp), *lpn = (double *)(w + p.lpn), *uu = (double *)(w + p.u);
     for (int32_t k = 0; k < n_steps; ++k) {
@@ -799,8 +819,6 @@ fn_status run_metropolis_group(const Ctx &c, const Plan &p, const void *theta, d
 {
     char *w = (char *)ws;
     const int n3 = 3 * c.s.N;
-    pack_weights<T>(c, p, (const T *)theta, w, st);
-    double *xp = (double *)(w + p.xp), *lpn = (double *)(w + p.lpn), *uu = (double *)(w + p.u);
     GroupTable g{};
     g.n = n_jobs;
     for (int q = 0; q < n_jobs; ++q) {
@@ -810,6 +828,16 @@ fn_status run_metropolis_group(const Ctx &c, const Plan &p, const void *theta, d
         g.stream[q] = jobs[q].stream_id;
     }
     g.w0[n_jobs] = B;
+    if constexpr (std::is_same<T, double>::value)
+        if (small_walk_supported(c.s, c.P, B)) {
+            for (int q = 0; q < n_jobs; ++q) g.step[q] = (uint32_t)jobs[q].step0;
+            Timed t_(K_STREAM_GEMM, st);
+            launch_small_walk(c.s, c.P, (const double *)theta, x, log_abs, nullptr, B, n_steps, sigma, g, nullptr, nullptr,
+                              n_accept, st);
+            return hip_status();
+        }
+    pack_weights<T>(c, p, (const T *)theta, w, st);
+    double *xp = (double *)(w + p.xp), *lpn = (double *)(w + p.lpn), *uu = (double *)(w + p.u);
     for (int32_t k = 0; k < n_steps; ++k) {
         for (int q = 0; q < n_jobs; ++q) g.step[q] = (uint32_t)(jobs[q].step0 + (uint64_t)k);
         {

@@ -160,6 +160,13 @@ struct GroupTable {
 };
 void launch_propose_group(const double *x, int64_t B, int n3, double sigma, const GroupTable &g, double *xp,
                           double *u, hipStream_t st);
+// log|psi| (n_steps = 0) and Metropolis moves of small FP64 networks in one
+// launch (fn_small.hip); g: the job table (one job of all walkers for a plain
+// walk), z / u: the caller's deviates or nullptr
+bool small_walk_supported(const Sys &s, const ParamLayout &P, int64_t B);
+void launch_small_walk(const Sys &s, const ParamLayout &P, const double *theta, double *x, double *log_abs, int8_t *sign,
+                       int64_t B, int n_steps, double sigma, const GroupTable &g, const double *z, const double *u,
+                       int32_t *n_accept, hipStream_t st);
 void launch_energy_stats(const double *e_loc, int64_t B, double *stats, double *coeff, hipStream_t st);
 
 }  // namespace fn
