@@ -375,6 +375,110 @@ __global__ __launch_bounds__(256) void k_gemm_splitk2(GemmArgs a0, GemmArgs a1, 
     else gemm_splitk_tile<MODE>(a1, (int64_t)blockIdx.x - nb0);
 }
 
+// Products whose 128-column tiles would leave CUs idle and whose reduction is
+// not split (split-BF16 modes): 32 x 64 output tiles, 2 x 2 waves of 16 x 32.
+// What bounds it: latency, a chain of reduction steps with little work each.
+// The tiled kernel meets at two barriers per step of 32; here the reduction goes
+// in chunks of 128 (64 with several weight parts), two chunks requested ahead.
+// (Fragments straight from global memory, without LDS, took 21 us where this
+// takes 10: 16 rows per load instruction.)  Same products in the same order per
+// output, transposed (D^T = W A^T), so that a lane stores four consecutive
+// columns.  Per-walker part of a layer, 512 x 256: 2048 walkers, six products
+// 22 -> 11 us; 4096 walkers, three products 20 -> 10 us.
+template <int MODE>
+__global__ __launch_bounds__(256, 2) void k_gemm_rows(GemmArgs a)
+{
+    constexpr int NA = ModeInfo<MODE>::NA, NW = ModeInfo<MODE>::NW;
+    constexpr int CS = NW == 1 ? 4 : 2, CK = 32 * CS;            // steps and inputs of a chunk
+    constexpr int AP = 32 * 32, WP = 64 * 32;                   // elements of one part of one step
+    __shared__ __attribute__((aligned(16))) uint16_t sA[CS * NA * AP], sW[CS * NW * WP];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 15, q = lane >> 4;
+    const int ncb = (a.nout + 63) / 64, kt = a.K1 + a.K2;
+    // column tiles of a row block 8 workgroups apart: same XCD, at the same time
+    const int bid = blockIdx.x, rem = bid % (8 * ncb);
+    const int64_t m0 = ((int64_t)(bid / (8 * ncb)) * 8 + (rem & 7)) * 32;
+    const int n0 = (rem >> 3) * 64;
+    if (m0 >= a.rows) return;
+    // operands of this thread: CS float4 of a row (8 threads along the step's 32
+    // inputs), CS uint4 of a weight row per part (4 threads); rows and columns past
+    // the end repeat the last one (not stored), inputs past the end the last step (not used)
+    const int xr = tid >> 3, xk = 4 * (tid & 7), wr = tid >> 2, wk = 8 * (tid & 3);
+    const int64_t ar = gemm_a_row(a, m0 + xr < a.rows ? m0 + xr : a.rows - 1);
+    const float *A1 = (const float *)a.A1 + ar * a.lda1, *A2 = (const float *)a.A2 + ar * a.lda2;
+    const uint16_t *W = (const uint16_t *)a.W + (int64_t)(n0 + wr < a.nout ? n0 + wr : a.nout - 1) * a.ldw + wk;
+    struct Chunk { float4 x[CS]; uint4 w[NW][CS]; };
+    auto load = [&](int kc) {
+        Chunk c;
+#pragma unroll
+        for (int h = 0; h < CS; ++h) {
+            const int kb = kc + 32 * h < kt ? kc + 32 * h : kt - 32, k = kb + xk;
+            c.x[h] = *(const float4 *)(k < a.K1 ? A1 + k : A2 + (k - a.K1));
+#pragma unroll
+            for (int p = 0; p < NW; ++p) c.w[p][h] = *(const uint4 *)(W + (int64_t)p * a.wpart + kb);
+        }
+        return c;
+    };
+    f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+    auto chunk = [&](const Chunk &c, int kc) {
+        __syncthreads();
+#pragma unroll
+        for (int h = 0; h < CS; ++h) {
+            uint32_t h01[NA], h23[NA];
+            split_bf16_pair<NA>(c.x[h].x, c.x[h].y, h01);
+            split_bf16_pair<NA>(c.x[h].z, c.x[h].w, h23);
+#pragma unroll
+            for (int p = 0; p < NA; ++p)
+                *(uint2 *)&sA[(h * NA + p) * AP + xr * 32 + 8 * lds_chunk(xr, xk >> 3) + (xk & 7)] = make_uint2(h01[p], h23[p]);
+#pragma unroll
+            for (int p = 0; p < NW; ++p) *(uint4 *)&sW[(h * NW + p) * WP + wr * 32 + 8 * lds_chunk(wr, wk >> 3)] = c.w[p][h];
+        }
+        __syncthreads();
+        const int ro = 16 * (wave >> 1) + r, co = 32 * (wave & 1) + r, ko = 8 * lds_chunk(r, q);
+#pragma unroll
+        for (int h = 0; h < CS; ++h) {
+            if (kc + 32 * h >= kt) break;
+            bf16x8 ha[NA], hw[NW][2];
+#pragma unroll
+            for (int p = 0; p < NA; ++p) ha[p] = *(const bf16x8 *)&sA[(h * NA + p) * AP + ro * 32 + ko];
+#pragma unroll
+            for (int p = 0; p < NW; ++p)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) hw[p][j] = *(const bf16x8 *)&sW[(h * NW + p) * WP + (co + 16 * j) * 32 + ko];
+#pragma unroll
+            for (int sum = NW == 1 ? 0 : NA - 1; sum >= 0; --sum)
+#pragma unroll
+                for (int pa = 0; pa <= (NW == 1 ? NA - 1 : sum); ++pa)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hw[NW == 1 ? 0 : sum - pa][j], ha[pa], acc[j], 0, 0, 0);
+        }
+    };
+    Chunk c0 = load(0), c1 = load(CK);
+    for (int kc = 0; kc < kt; kc += 2 * CK) {
+        chunk(c0, kc);
+        c0 = load(kc + 2 * CK);
+        if (kc + CK >= kt) break;
+        chunk(c1, kc + CK);
+        c1 = load(kc + 3 * CK);
+    }
+    int64_t row = m0 + 16 * (wave >> 1) + r;
+    if (row >= a.rows) return;
+    if (a.c_rows_per_group > 0) row = remap_row(row, a.c_rows_per_group, a.c_group_stride, a.c_row_offset);
+    float *C = (float *)a.C + row * a.ldc;
+    const bool vec = a.ldc % 4 == 0 && ((uintptr_t)a.C & 15) == 0;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int col = n0 + 32 * (wave & 1) + 16 * j + 4 * q;
+        if (vec && col + 3 < a.nout) {
+            *(f32x4 *)(C + col) = acc[j];
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (col + e < a.nout) C[col + e] = acc[j][e];
+        }
+    }
+}
+
 // FP64 on the matrix cores (v_mfma_f64_16x16x4_f64, accumulator element e at
 // row 4 e + lane / 16, column lane % 16).  Reduction index of an operand
 // fragment: lane group g = lane / 16 holds the pair 2 g, 2 g + 1 of eight
@@ -574,7 +678,8 @@ static void launch_bn(int mode, const GemmArgs &a, const GemmArgs *a1, hipStream
 }
 
 // narrowest column tile that covers the output, and narrower still when
-// 128-column tiles would leave CUs idle (latency-bound small grids)
+// 128-column tiles would leave CUs idle (latency-bound small grids; the split-BF16
+// modes then take k_gemm_rows for more than 32 columns)
 static int pick_bn(const GemmArgs &a)
 {
     const int64_t nrb = (a.rows + BM - 1) / BM;
@@ -609,10 +714,23 @@ static void launch_splitk(int mode, const GemmArgs &a, const GemmArgs *a1, hipSt
     with_split_mode(mode, [&](auto m) { launch_splitk_mode<decltype(m)::value>(a, a1, st); });
 }
 
+static void launch_rows(int mode, const GemmArgs &a, hipStream_t st)
+{
+    const int64_t nrb8 = (a.rows + 255) / 256;
+    const dim3 grid((unsigned)(nrb8 * 8 * ((a.nout + 63) / 64)));
+    with_split_mode(mode, [&](auto m) { hipLaunchKernelGGL((k_gemm_rows<decltype(m)::value>), grid, dim3(256), 0, st, a); });
+}
+
 static void launch_mfma(int mode, const GemmArgs &a, const GemmArgs *a1, hipStream_t st)
 {
     if (use_splitk(mode, a) && (!a1 || use_splitk(mode, *a1))) {
         launch_splitk(mode, a, a1, st);
+        return;
+    }
+    // (two products in one launch stay with the tiled kernel: the orbital heads of
+    // 4096 walkers, 8 steps of 96 columns, 22.9 us there and 22.4 in this form)
+    if (mode != GEMM_F32 && !a1 && pick_bn(a) == 32 && a.nout > 32 && a.K1 + a.K2 > 0) {
+        launch_rows(mode, a, st);
         return;
     }
     switch (pick_bn(a)) {
