@@ -520,6 +520,7 @@ void forward_chunk(const Ctx &c, const Plan &p, const T *theta, const double *xw
             }
             Timed t_(K_STREAM_GEMM, st);
             if (walk) launch_walk_layer(c.smode, la, TR, b, st);
+            else if (TR == 1 && walk_value_supported(c.smode, la)) launch_walk_value(c.smode, la, st);
             else launch_stream_layer(c.smode, la, TR, st);
         }
         if (!fused) {

@@ -476,6 +476,9 @@ void launch_stream_layer(int mode, const LayerArgs &a, int TR, hipStream_t st);
 // electrons.
 bool walk_layer_supported(int mode, const LayerArgs &a, int TR, int64_t B);
 void launch_walk_layer(int mode, const LayerArgs &a, int TR, int64_t B, hipStream_t st);
+// value rows only (TR = 1; bitwise the tiled kernel's results)
+bool walk_value_supported(int mode, const LayerArgs &a);
+void launch_walk_value(int mode, const LayerArgs &a, hipStream_t st);
 
 // Every one-electron layer of a forward-Laplacian pass in one kernel
 // (fn_stack.hip), for two to four electrons (TR = 16) and w1 = 256.

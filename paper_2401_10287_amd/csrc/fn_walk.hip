@@ -323,7 +323,178 @@ __global__ __launch_bounds__(64 * WALK_WAVES, 2) void k_walk_layer(LayerArgs a, 
     }
 }
 
+// The same layer on value rows only (no derivatives: log|psi| and Metropolis
+// moves), flat rows of any number of electrons.  What bounds it: the vector ALUs
+// (tanh of every output, the splits) about level with the matrix cores and the
+// traffic of h.  As above weights stay in registers, rows are split once for a
+// workgroup's columns, and the products are transposed; a tile is 32 rows, rows
+// past the end repeat the last one (its outputs are stored again).
+// Tiled -> here, a 256-wide layer: 12 electrons, 4096 walkers, three products 60
+// -> 40 us (the features' layer 35 -> 21); 10 electrons, 2048 walkers, six
+// products 38 -> 33 us.
+template <int MODE, int KS>
+struct ValueShape {
+    static constexpr int NA = act_parts(MODE), NW = weight_parts(MODE);
+    static constexpr int WJ = NW == 1 ? 2 : 1;
+    static constexpr int NCG = 256 / (16 * WJ * WALK_WAVES);
+    static constexpr int D = KS == 10 ? 5 : KS, SP = 2;
+    static constexpr int PART = 2 * 16 * 64, STEP = NA * PART;
+    static constexpr int K1 = KS == 10 ? 256 : 32 * (KS - 1);
+    static constexpr bool RESID = KS == 10;
+};
+
+template <int MODE, int KS>
+__global__ __launch_bounds__(64 * WALK_WAVES, 2) void k_walk_value(LayerArgs a)
+{
+    typedef ValueShape<MODE, KS> S;
+    constexpr int NA = S::NA, NW = S::NW, WJ = S::WJ, D = S::D, LD = 256;
+    __shared__ __attribute__((aligned(16))) unsigned char smem[2 * S::SP * S::STEP];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int bid = blockIdx.x;
+    const int cg = (bid >> 3) % S::NCG;
+    const int64_t tiles = (a.rows + 31) / 32;
+    const int blk = (bid & 7) + 8 * (bid / (8 * S::NCG)), nblk = gridDim.x / S::NCG;
+    if (blk >= tiles) return;
+    const int r = lane & 15, q = lane >> 4;
+    const int n0 = (cg * WALK_WAVES + wave) * 16 * WJ;
+
+    bf16x8 hb[KS][NW][WJ];
+#pragma unroll
+    for (int k = 0; k < KS; ++k)
+#pragma unroll
+        for (int p = 0; p < NW; ++p)
+#pragma unroll
+            for (int j = 0; j < WJ; ++j)
+                hb[k][p][j] = *(const bf16x8 *)((const uint16_t *)a.W + (int64_t)p * a.wpart +
+                                                (int64_t)(n0 + 16 * j + r) * a.ldw + 32 * k + 8 * q);
+    f32x4 bb[WJ];
+#pragma unroll
+    for (int j = 0; j < WJ; ++j) bb[j] = *(const f32x4 *)(a.bias + n0 + 16 * j + 4 * q);
+
+    const int srow = tid >> 3, sk = 4 * (tid & 7);
+    const int swr = srow * 64 + 16 * lds_chunk(srow, sk >> 3) + 2 * (sk & 7);
+    const int srd = r * 64 + 16 * lds_chunk(r, q);
+    auto clamp = [&](int64_t row) { return row < a.rows ? row : a.rows - 1; };
+    auto load = [&](int64_t t, int k) {
+        const int64_t row = clamp(32 * t + srow);
+        return *(const float4 *)(32 * k < S::K1 ? a.A1 + row * LD + 32 * k + sk : a.A2 + row * a.lda2 + (32 * k - S::K1) + sk);
+    };
+    auto stage = [&](float4 x, int slot) {
+        unsigned char *d = smem + slot * S::STEP + swr;
+        uint32_t a01[NA], a23[NA];
+        split_bf16_pair<NA>(x.x, x.y, a01);
+        split_bf16_pair<NA>(x.z, x.w, a23);
+#pragma unroll
+        for (int p = 0; p < NA; ++p) *(uint2 *)(d + p * S::PART) = make_uint2(a01[p], a23[p]);
+    };
+    // the tile that follows tile t; after the last one that one again
+    auto next = [&](int64_t t) { return t + nblk < tiles ? t + nblk : t; };
+    int64_t t0 = blk, t1 = next(t0), t2 = next(t1);
+    float4 pre[D];
+#pragma unroll
+    for (int k = 0; k < D; ++k) pre[k] = load(t0, k);
+#pragma unroll
+    for (int k = 0; k < S::SP; ++k) {
+        stage(pre[k], k);
+        pre[k] = D + k < KS ? load(t0, D + k) : load(t1, D + k - KS);
+    }
+    lds_barrier();
+    int cur = 0;
+    for (int64_t t = blk; t < tiles; t += nblk) {
+        f32x4 acc[2][WJ], pw[2][WJ], rs[2][WJ];
+        int64_t row[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            row[i] = clamp(32 * t + 16 * i + r);
+            const int64_t w = row[i] / a.N;
+#pragma unroll
+            for (int j = 0; j < WJ; ++j) {
+                acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                pw[i][j] = *(const f32x4 *)(a.Pw + w * LD + n0 + 16 * j + 4 * q);
+                if constexpr (S::RESID) rs[i][j] = *(const f32x4 *)(a.A1 + row[i] * LD + n0 + 16 * j + 4 * q);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            const int h = k % S::SP, n = k + S::SP;       // n: step staged now, n + D: step requested now
+            const unsigned char *sa = smem + (S::SP * cur + h) * S::STEP + srd;
+            bf16x8 ha[NA][2];
+#pragma unroll
+            for (int p = 0; p < NA; ++p)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) ha[p][i] = *(const bf16x8 *)(sa + p * S::PART + i * 1024);
+            __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+            for (int sum = NW == 1 ? 0 : NA - 1; sum >= 0; --sum)
+#pragma unroll
+                for (int pa = 0; pa <= (NW == 1 ? NA - 1 : sum); ++pa)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int j = 0; j < WJ; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hb[k][NW == 1 ? 0 : sum - pa][j], ha[pa][i],
+                                                                                acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_s_setprio(0);
+            stage(pre[n % D], S::SP * (cur ^ 1) + h);
+            pre[n % D] = n + D < KS ? load(t0, n + D) : (n + D < 2 * KS ? load(t1, n + D - KS) : load(t2, n + D - 2 * KS));
+            if (h == S::SP - 1) {
+                lds_barrier();
+                cur ^= 1;
+            }
+        }
+        t0 = t1; t1 = t2; t2 = next(t2);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < WJ; ++j) {
+                f32x4 y;
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    const float v = tanhf((acc[i][j][x] + pw[i][j][x]) + bb[j][x]);
+                    if constexpr (S::RESID) y[x] = v + rs[i][j][x];
+                    else y[x] = v + 0.f;
+                }
+                *(f32x4 *)(a.Hout + row[i] * LD + n0 + 16 * j + 4 * q) = y;
+            }
+    }
+}
+
 }  // namespace
+
+// Widths and reduction steps of walk_layer_supported; the spin means are left to
+// their own pass, so not where the tiled kernels write them.  Below 4096 rows the
+// reduction may be split over waves (other bits).  log|psi|, tiled -> here (us):
+// 12 electrons, BF16 weights, 342 walkers (4104 rows) 170 -> 153, 1024 200 -> 188;
+// 10 electrons, six products, 410 161 -> 148, 1024 189 -> 179.
+bool walk_value_supported(int mode, const LayerArgs &a)
+{
+    const int ks = (a.K1 + a.K2) / 32;
+    return (mode == GEMM_BF16W3 || mode == GEMM_BF16X6) && !a.Gout && a.w1 == 256 && a.W1p == 256 && a.lda1 == 256 &&
+           a.ldh_out == 256 && a.nout == 256 && a.resid == (ks == 10) &&
+           (ks == 10 ? a.K1 == 256 : (ks == 2 || ks == 4) && a.K2 == 32) && a.rows >= 4096;
+}
+
+template <int MODE>
+static void launch_value_mode(const LayerArgs &a, hipStream_t st)
+{
+    const int64_t tiles = (a.rows + 31) / 32;
+    auto go = [&](auto ks) {
+        constexpr int KS = decltype(ks)::value, NCG = ValueShape<MODE, KS>::NCG;
+        const int64_t nb = tiles < 512 / NCG ? (tiles + 7) / 8 * 8 : 512 / NCG;
+        hipLaunchKernelGGL((k_walk_value<MODE, KS>), dim3((unsigned)(nb * NCG)), dim3(64 * WALK_WAVES), 0, st, a);
+    };
+    const int ks = (a.K1 + a.K2) / 32;
+    if (ks == 2) go(std::integral_constant<int, 2>{});
+    else if (ks == 4) go(std::integral_constant<int, 4>{});
+    else go(std::integral_constant<int, 10>{});
+}
+
+void launch_walk_value(int mode, const LayerArgs &a, hipStream_t st)
+{
+    if (mode == GEMM_BF16W3) launch_value_mode<GEMM_BF16W3>(a, st);
+    else launch_value_mode<GEMM_BF16X6>(a, st);
+}
 
 // Walkers whose workgroups run at the same time: two per CU (76 KB of LDS, 256
 // registers), one per walker and column group.

@@ -37,3 +37,28 @@ def test_small_grid_products(w1, precision, walkers):
         fnvmc.fn_tuning_set("gemm_splitk", 1)
     assert torch.isfinite(small).all()
     assert torch.equal(small, big[:walkers]) and torch.equal(ls, lb[:walkers])
+
+
+# value rows of the 256-wide layers: the first, middle and last layer's reductions
+# (features of 2 and of 20 nuclei, pair means), rows that end inside a tile, fewer
+# and more tiles than workgroups; the small batch is under the kernel's 4096 rows
+@pytest.mark.parametrize("nuclei,spins,precision,walkers", [(2, (3, 2), "bf16w", 901), (2, (3, 2), "bf16x6", 820),
+                                                            (20, (4, 3), "bf16w", 3001), (20, (4, 3), "bf16x6", 3003)])
+def test_value_rows(nuclei, spins, precision, walkers):
+    import torch
+    from paper_2401_10287_amd import fnvmc
+    n = sum(spins)
+    s = I.System("S", np.array([[0.0, 0.1 * i, 1.4 * i] for i in range(nuclei)]), np.full(nuclei, 2.0), spins[0], spins[1],
+                 3, 256, 32, 2, 1, tuple(i % nuclei for i in range(n)), 1.0)
+    cfg = fnvmc.Config(s, precision)
+    tt = torch.tensor(I.init_params(s), dtype=cfg.param_dtype, device="cuda")
+    x = torch.tensor(I.init_walkers(s, walkers), device="cuda")
+    try:
+        fnvmc.fn_tuning_set("gemm_splitk", 0)
+        big, sb = fnvmc.fn_log_psi(cfg, tt, x)
+        tail, st = fnvmc.fn_log_psi(cfg, tt, x[-257:].contiguous())
+        torch.cuda.synchronize()
+    finally:
+        fnvmc.fn_tuning_set("gemm_splitk", 1)
+    assert torch.isfinite(big).all()
+    assert torch.equal(tail, big[-257:]) and torch.equal(st, sb[-257:])
