@@ -689,6 +689,7 @@ __global__ __launch_bounds__(256) void k_pair_backward_mfma(Sys s, const double 
 // TN_PF such steps requested ahead.  The four waves of a workgroup take
 // consecutive parts of the split's rows and are added in wave order; all tiles
 // of a split follow each other on one XCD, so its rows come from HBM once.
+// A single split (ONE) is added to the gradient here.
 // (A workgroup per 64 x 64 tile with 64 rows staged in LDS per barrier: 12
 // electrons, 4096 walkers, the gradient's 18 products 855 -> 590 us; FP64, 2
 // electrons, 256 walkers, ten products 722 -> 58 us.)
@@ -703,16 +704,18 @@ __device__ __forceinline__ f32x4 tn_mfma(float a, float b, f32x4 c) { return __b
 __device__ __forceinline__ f64x4 tn_mfma(double a, double b, f64x4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
 constexpr int TN_PF = 4;
 
-template <typename T>
+template <typename T, bool ONE>
 __global__ __launch_bounds__(256) void k_tn_partial(const T *__restrict__ X, int64_t ldx, int NA, const T *__restrict__ Y,
                                                     int64_t ldy, int NB, int64_t R, int64_t per, int64_t stride,
-                                                    int64_t off, int64_t rows_per_split, int S, T *__restrict__ part)
+                                                    int64_t off, int64_t rows_per_split, int S, T *__restrict__ part,
+                                                    double *__restrict__ out, int64_t out_off, int64_t lda_out)
 {
     typedef TnTile<T> H;
     typedef typename H::vec vec;
     typedef typename H::acc accv;
     constexpr int V = H::V, W = H::W, PF = TN_PF;
     __shared__ accv red[3][V][64];
+    __shared__ T sum[ONE ? W : 1][W + V];                                // the tile, where it goes straight to the gradient
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nta = (NA + W - 1) / W, tiles = nta * ((NB + W - 1) / W);
     const int idx = (int)(blockIdx.x >> 3), sp = (idx / tiles) * 8 + (int)(blockIdx.x & 7), tile = idx % tiles;
@@ -745,6 +748,17 @@ __global__ __launch_bounds__(256) void k_tn_partial(const T *__restrict__ X, int
             yv[u] = y;
         }
     };
+    // (ONE) one split: the gradient's entries, requested before the rows
+    constexpr int NV = W * W / 256;
+    double old[NV];
+    int64_t dst[NV];
+    if constexpr (ONE)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const int q = threadIdx.x + 256 * v, a = a0 + q / W, b = b0 + q % W;
+            dst[v] = a < NA && b < NB ? out_off + (int64_t)a * lda_out + b : -1;
+            old[v] = out[dst[v] >= 0 ? dst[v] : out_off];
+        }
     if (r0 < r1) load(r0);
     for (int64_t rb = r0; rb < r1; rb += 4 * PF) {
         vec x[PF], y[PF];
@@ -776,12 +790,24 @@ __global__ __launch_bounds__(256) void k_tn_partial(const T *__restrict__ X, int
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int a = a0 + V * (sizeof(T) == 4 ? 4 * g + e : 4 * e + g) + i;
+            if constexpr (ONE) {
+#pragma unroll
+                for (int j = 0; j < V; ++j) sum[a - a0][V * m + j] = acc[i][j][e];
+                continue;
+            }
             if (a >= NA) continue;
             T *q = p + (int64_t)a * NB + b0 + V * m;
 #pragma unroll
             for (int j = 0; j < V; ++j)
                 if (b0 + V * m + j < NB) q[j] = acc[i][j][e];
         }
+    }
+    if constexpr (!ONE) return;
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const int q = threadIdx.x + 256 * v;
+        if (dst[v] >= 0) out[dst[v]] = old[v] + (double)sum[q / W][q % W];
     }
 }
 
@@ -1043,8 +1069,16 @@ void launch_tn(const T *X, int64_t ldx, int NA, const T *Y, int64_t ldy, int NB,
     S = std::min<int64_t>(S, part_elems / ((int64_t)NA * NB));       // the partials' buffer
     if (S < 1) S = 1;
     const int64_t rps = (R + S - 1) / S;
-    hipLaunchKernelGGL(k_tn_partial<T>, dim3((unsigned)((S + 7) / 8 * 8 * tiles)), dim3(256), 0, st, X, ldx, NA, Y, ldy, NB,
-                       R, per, stride, off, rps, (int)S, part);
+    const dim3 grid((unsigned)((S + 7) / 8 * 8 * tiles));
+    // fewer than 256 rows: one split, added to the gradient where it is formed
+    // (gradient of 10 electrons, 2 walkers: 515 -> 501 us)
+    if (S == 1) {
+        hipLaunchKernelGGL((k_tn_partial<T, true>), grid, dim3(256), 0, st, X, ldx, NA, Y, ldy, NB, R, per, stride, off, rps, 1,
+                           part, acc, acc_off, lda_out);
+        return;
+    }
+    hipLaunchKernelGGL((k_tn_partial<T, false>), grid, dim3(256), 0, st, X, ldx, NA, Y, ldy, NB, R, per, stride, off, rps,
+                       (int)S, part, acc, acc_off, lda_out);
     hipLaunchKernelGGL(k_tn_reduce<T>, dim3(gridn((int64_t)NA * NB)), dim3(256), 0, st, part, (int)S, NA, NB, acc, acc_off,
                        lda_out);
 }
