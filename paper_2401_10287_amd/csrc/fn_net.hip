@@ -965,6 +965,71 @@ __global__ __launch_bounds__(64) void k_det(const T *Phi, int64_t B, int K, int 
     if (lane == 0) out[2 + n3] = trl - sq;
 }
 
+// Value form of up to 10 electrons: a thread per (walker, determinant), the matrix
+// in registers, the same elimination.  What bounds it: reading the matrices.  (A
+// wave per matrix searches its pivots in one lane, a column at a time through
+// LDS.)  6 electrons per spin, 65536 matrices: 133 -> 10 us.
+template <int n>
+__global__ __launch_bounds__(64) void k_det_lanes(const double *__restrict__ Phi, int64_t B, int K, int TR, int sp,
+                                                  double *__restrict__ DR, int rec)
+{
+    const int64_t wk = blockIdx.x * (int64_t)64 + threadIdx.x;
+    if (wk >= B * K) return;
+    const double *A = Phi + wk * TR * (n * n);
+    double v[n][n];
+#pragma unroll
+    for (int r = 0; r < n; ++r)
+#pragma unroll
+        for (int q = 0; q < n; ++q) v[r][q] = A[r * n + q];
+    bool sing = false;
+    int sign = 1;
+    double lg = 0.0;
+#pragma unroll
+    for (int c = 0; c < n; ++c) {
+        int p = c;
+        double best = fabs(v[c][c]);
+#pragma unroll
+        for (int r = c + 1; r < n; ++r) {
+            const double t = fabs(v[r][c]);
+            if (t > best) { best = t; p = r; }
+        }
+        sing = sing || best == 0.0;
+#pragma unroll
+        for (int r = c + 1; r < n; ++r) {
+            const bool sw = p == r;
+#pragma unroll
+            for (int q = c; q < n; ++q) {
+                const double t = v[c][q];
+                v[c][q] = sw ? v[r][q] : t;
+                v[r][q] = sw ? t : v[r][q];
+            }
+        }
+        if (p != c) sign = -sign;
+        if (v[c][c] < 0.0) sign = -sign;
+        lg += log(fabs(v[c][c]));
+        const double ip = 1.0 / v[c][c];
+#pragma unroll
+        for (int r = c + 1; r < n; ++r) {
+            const double f = v[r][c] * ip;
+#pragma unroll
+            for (int q = c + 1; q < n; ++q) v[r][q] -= f * v[c][q];
+        }
+    }
+    double *out = DR + ((wk / K) * 2 + sp) * (int64_t)K * rec + (wk % K) * rec;
+    if (sing) {
+        for (int q = 0; q < rec; ++q) out[q] = q == 0 ? 0.0 : (q == 1 ? -INFINITY : NAN);
+        return;
+    }
+    out[0] = (double)sign;
+    out[1] = lg;
+}
+
+template <int n>
+static void launch_det_lanes(const double *Phi, int64_t B, int K, int TR, int sp, double *DR, int rec, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_det_lanes<n>, dim3((unsigned)((B * K + 63) / 64)), dim3(64), 0, st, Phi, B, K, TR, sp, DR, rec);
+}
+
 // ---------------------------------------------------------------------------
 // forward-Laplacian orbitals, envelope and determinant in one pass: one
 // wave64 per (walker, determinant k) of one spin.  The orbital matrix and its
@@ -1858,6 +1923,20 @@ void launch_det(const double *Phi, int64_t B, int K, int n, int TR, int n3, int 
                 hipStream_t st)
 {
     typedef double T;
+    // (a matrix of 11 or more no longer fits the 256 registers of a lane at two waves per SIMD)
+    if (!fl) switch (n) {
+        case 1: return launch_det_lanes<1>(Phi, B, K, TR, sp, DR, rec, st);
+        case 2: return launch_det_lanes<2>(Phi, B, K, TR, sp, DR, rec, st);
+        case 3: return launch_det_lanes<3>(Phi, B, K, TR, sp, DR, rec, st);
+        case 4: return launch_det_lanes<4>(Phi, B, K, TR, sp, DR, rec, st);
+        case 5: return launch_det_lanes<5>(Phi, B, K, TR, sp, DR, rec, st);
+        case 6: return launch_det_lanes<6>(Phi, B, K, TR, sp, DR, rec, st);
+        case 7: return launch_det_lanes<7>(Phi, B, K, TR, sp, DR, rec, st);
+        case 8: return launch_det_lanes<8>(Phi, B, K, TR, sp, DR, rec, st);
+        case 9: return launch_det_lanes<9>(Phi, B, K, TR, sp, DR, rec, st);
+        case 10: return launch_det_lanes<10>(Phi, B, K, TR, sp, DR, rec, st);
+        default: break;
+        }
     size_t lds = det_lds(n, n3, fl, sizeof(T));
     dim3 g((unsigned)(B * K));
     if (fl)
