@@ -22,7 +22,7 @@
 //               the exact hi + mid + lo split of the FP32 activations: three
 //               products, each exact, accumulated in FP32
 //   GEMM_BF16W2 BF16 weights times the hi + lo split of the activations
-//   GEMM_F64    v_mfma_f64_16x16x4_f64, FP64 operands (64 x 64 tiles, 16 x 16 for small grids)
+//   GEMM_F64    v_mfma_f64_16x16x4_f64, FP64 operands (128-row tiles, 16 x 16 for small grids)
 #include "fn_internal.h"
 
 namespace fn {
