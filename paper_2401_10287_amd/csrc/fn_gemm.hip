@@ -618,8 +618,9 @@ __global__ __launch_bounds__(64) void k_gemm_f64_small(GemmArgs a)
             xw[v] = *(const f64x2 *)(pw + kb + 8 * v);
         }
     };
-    // two chains of sums, added at the end
-    f64x4 c0 = {0.0, 0.0, 0.0, 0.0}, c1 = {0.0, 0.0, 0.0, 0.0};
+    // one chain in the tiled kernel's order (pair element 0, then 1, of ascending
+    // groups of eight): an output's bits do not depend on the grid
+    f64x4 c = {0.0, 0.0, 0.0, 0.0};
     if (K > 0) load(0);
     for (int kb = 0; kb < K; kb += 32) {
         f64x2 fa[4], fw[4];
@@ -628,8 +629,8 @@ __global__ __launch_bounds__(64) void k_gemm_f64_small(GemmArgs a)
         if (kb + 32 < K) load(kb + 32);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            c0 = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[v][0], fw[v][0], c0, 0, 0, 0);
-            c1 = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[v][1], fw[v][1], c1, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[v][0], fw[v][0], c, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[v][1], fw[v][1], c, 0, 0, 0);
         }
     }
     double *C = (double *)a.C;
@@ -639,7 +640,7 @@ __global__ __launch_bounds__(64) void k_gemm_f64_small(GemmArgs a)
         int64_t row = m0 + 4 * e + (lane >> 4);
         if (row >= a.rows || col >= a.nout) continue;
         if (a.c_rows_per_group > 0) row = remap_row(row, a.c_rows_per_group, a.c_group_stride, a.c_row_offset);
-        C[row * a.ldc + col] = c0[e] + c1[e];
+        C[row * a.ldc + col] = c[e];
     }
 }
 
