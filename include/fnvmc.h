@@ -194,7 +194,8 @@ fn_status vmc_metropolis_step_noalloc(const fn_config *cfg, const void *theta, d
    tile 0 .. B_total - 1 in order, without gaps) and draws its random numbers
    exactly as vmc_metropolis_step(seed, step0, stream_id) does for its own
    walkers 0 .. B - 1.  The kernels take the same path at every batch size
-   (the small-batch split-reduction products are not used), so each job's
+   (the small-batch split-reduction products are not used, and the one-launch
+   kernel of small FP64 networks is chosen by the network alone), so each job's
    results are bitwise those it gets in a group of its own, and those of
    vmc_metropolis_step with the "gemm_splitk" switch off.  jobs: host
    [n_jobs], 1 <= n_jobs <= FN_MAX_GROUP_JOBS.  Workspace:
@@ -390,7 +391,11 @@ fn_status fn_timing_read(const char *name, double *total_ms, int64_t *launches);
    stream layers whose 128-row tiles would not fill the CUs (small walker
    batches in the value form) run as 32 x 32 tiles with the reduction split
    over the workgroup's four waves and summed in wave order (default 1), or
-   as the tiled kernels; the two differ in summation order only.
+   as the tiled kernels; the two differ in summation order only.  In FP64,
+   log|psi| and moves of small networks (up to 4 electrons, w1 <= 64, w2 <= 32,
+   16 determinants, parameters within 64 KB) run in one launch up to a batch
+   limit (default 1), or at every batch size or none, by the network alone
+   (0); the one launch and the layers' kernels differ in summation order only.
    "gemm_wide" 0/1: products of 65..96 output columns (the orbital head of
    spins with 5 or 6 electrons) take 96-column tiles (default 1) or
    128-column tiles; results are bitwise equal.

@@ -268,12 +268,20 @@ int small_waves(const Sys &s, const ParamLayout &P, int64_t B)
 // four rounds of the walkers that the chip holds at once (256 CUs of 160 KB): a
 // round costs the same again, the layers' own kernels only their rows.  Measured
 // here / layer by layer, us per log|psi|: 4500 parameters, 4096 walkers 31 / 85,
-// 16384 (six rounds) 94 / 142; 6950 parameters (one walker per workgroup), 1024
-// walkers 48 / 82, 2048 (four rounds) 92 / 96, 4096 181 / 115.
+// 16384 (six rounds) 94 / 142; 7073 parameters (one walker per workgroup), 1024
+// walkers 48 / 82, 2048 (four rounds) 92 / 95, 4096 181 / 116.
+// Where results must not depend on the batch (grouped and served calls, "gemm_splitk"
+// off) the network alone decides: four walkers of a workgroup have to fit.  Ten
+// moves of such networks, group of 256 / 4096 / 65536: 4500 parameters 121 / 275 /
+// 3554 here, 698 / 868 / 4020 layer by layer; 5484 parameters (about the
+// most that fit) 164 / 415 / 6028 and 734 / 974 / 4595 (level at 16384).  Larger ones (one or two
+// walkers) lose from about 2000 walkers on: 7073 parameters, 256 / 2048 / 16384:
+// 210 / 834 / 6527 and 762 / 969 / 2872.
 bool small_walk_supported(const Sys &s, const ParamLayout &P, int64_t B)
 {
     if (s.N > SM_ELEC || s.w1 > SM_W1 || s.w2 > SM_W2 || s.K > SM_DET) return false;
     if (small_lds(s, P, 1) > 64 * 1024) return false;
+    if (g_splitk_suppressed || !g_gemm_splitk) return small_lds(s, P, 4) <= 64 * 1024;
     const int nw = small_waves(s, P, B);
     return B <= 4 * 256 * (int64_t)(160 * 1024 / small_lds(s, P, nw)) * nw;
 }

@@ -62,3 +62,16 @@ def test_energy_of_small_and_large_batches(w1, walkers):
     assert torch.isfinite(big).all()
     assert torch.equal(small, big[-19:]) and torch.equal(ls, lb[-19:])
     assert torch.equal(vs, v[-19:]) and torch.equal(ss, sg[-19:])
+
+
+# networks that the one-launch kernel takes up to a batch limit, groups beyond it:
+# 12288 walkers where four share a workgroup's parameters, 2048 where one fits
+@pytest.mark.parametrize("w1,w2,dets,spins,nuclei,jobs", [
+    (32, 8, 2, (1, 1), 1, [(256, 3, 0, 1), (37, 5, 11, 2), (12300, 3, 4, 9)]),
+    (37, 4, 6, (2, 2), 2, [(100, 3, 0, 1), (256, 5, 11, 2), (2500, 3, 4, 9)])])
+def test_group_of_a_small_network(w1, w2, dets, spins, nuclei, jobs):
+    import numpy as np
+    n = sum(spins)
+    s = I.System("S", np.array([[0.0, 0.3 * i, 1.9 * i] for i in range(nuclei)]), np.full(nuclei, 2.0), spins[0], spins[1],
+                 2, w1, w2, dets, 1, tuple(i % nuclei for i in range(n)), 1.0)
+    _group_equals_alone_and_plain(s, jobs, 4)
