@@ -596,9 +596,9 @@ __global__ __launch_bounds__(256, 2) void k_gemm_f64(GemmArgs a)
         }
 }
 
-// Grids of fewer 128 x 64 tiles than CUs: bound by the latency of one tile.  A
-// wave takes a 16 x 16 tile with its fragments straight from memory, 32
-// reduction indices (four pairs of each operand per lane) requested ahead.
+// Small grids: bound by the latency of one tile.  A wave takes a 16 x 16 tile with
+// its fragments straight from memory, 32 reduction indices (four pairs of each
+// operand per lane) requested ahead.
 // 512 rows x 64 x 32: 14 us on the tiled vector kernel, 5 us here.
 __global__ __launch_bounds__(64) void k_gemm_f64_small(GemmArgs a)
 {
@@ -754,7 +754,12 @@ hipError_t launch_gemm(int mode, const GemmArgs &a, hipStream_t st)
             const int64_t blocks = ncb <= 2 ? xcd_grid(nrb, ncb) : nrb * ncb;
             hipLaunchKernelGGL((k_gemm_f64<BN>), dim3((unsigned)blocks), dim3(256), 0, st, a);
         };
-        if (nrb * ((a.nout + 63) / 64) < 256)
+        // Small while its 16 x 16 tiles are 3584 waves or fewer, 14 a CU (the bits are the
+        // same in both).  Tiled / small, us a product of a value layer at 3072 and at 4096
+        // waves: 64 columns 14.9 / 13.9 and 15.0 / 15.4; 128 18.5 / 17.9 and 18.4 / 20.7;
+        // 256 23.0 / 22.0 and 23.4 / 27.5; 512 33.2 / 32.4 and 33.5 / 41.1; 32 13.6 / 12.2 and
+        // 13.4 / 13.3.  Local energies at 3584: 4 electrons, 64 wide, 256 walkers 207 / 196.
+        if (((a.rows + 15) / 16) * ((a.nout + 15) / 16) <= 3584)
             hipLaunchKernelGGL(k_gemm_f64_small, dim3((unsigned)((a.rows + 15) / 16), (unsigned)((a.nout + 15) / 16)), dim3(64),
                                0, st, a);
         else if (a.nout <= 64 || nrb * ((a.nout + 127) / 128) < 256) tiled(std::integral_constant<int, 64>{});
