@@ -175,10 +175,13 @@ __global__ __launch_bounds__(64 * DET_WAVES) void k_orbdet_lanes(Sys s, const do
         mypiv = lane == c ? fabs(f[c]) : mypiv;
         const double ip = 1.0 / f[c];
         if constexpr (FL) {
-            v[c] *= ip;
+            // multipliers first, as in the value form: pivots, sign and log|det| are then the
+            // same bits there (with v[c] scaled first, equal columns can cancel to exact zeros
+            // that the value form does not get: a node here and a finite log|psi| there)
 #pragma unroll
             for (int r = 0; r < NS; ++r)
-                if (r != c) v[r] -= f[r] * v[c];
+                if (r != c) v[r] -= (f[r] * ip) * v[c];
+            v[c] *= ip;
         } else {
 #pragma unroll
             for (int r = c + 1; r < NS; ++r) v[r] -= (f[r] * ip) * v[c];
