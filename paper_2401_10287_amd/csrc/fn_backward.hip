@@ -15,11 +15,11 @@
 // Weight gradients are sums over walkers x electrons of outer products; they
 // are formed as split row reductions whose partial sums are added in a fixed
 // order, so the result does not depend on scheduling.
-#include <algorithm>
 #include <type_traits>
 
 #include "fn_internal.h"
 #include "fn_kernels.h"
+#include "fn_rules.h"
 
 namespace fn {
 
@@ -1052,7 +1052,7 @@ int tn_splits(int64_t R)
 {
     int64_t s = R / 512;
     if (s < 1) s = 1;
-    if (s > 64) s = 64;
+    if (s > MAX_SPLITS) s = MAX_SPLITS;
     return (int)s;
 }
 
@@ -1064,13 +1064,11 @@ void launch_tn(const T *X, int64_t ldx, int NA, const T *Y, int64_t ldy, int NB,
     if (R <= 0 || NA <= 0 || NB <= 0) return;
     constexpr int W = TnTile<T>::W;
     const int tiles = ((NA + W - 1) / W) * ((NB + W - 1) / W);
-    // three workgroups per CU where the rows give them, 32 rows per wave or more
-    int64_t S = std::min<int64_t>(std::min<int64_t>(768 / tiles + 1, max_splits()), R / 128);
-    S = std::min<int64_t>(S, part_elems / ((int64_t)NA * NB));       // the partials' buffer
-    if (S < 1) S = 1;
+    const int64_t S = tn_product_splits(R, tiles, part_elems / ((int64_t)NA * NB));
     const int64_t rps = (R + S - 1) / S;
     const dim3 grid((unsigned)((S + 7) / 8 * 8 * tiles));
-    // fewer than 256 rows: one split, added to the gradient where it is formed
+    // one split (fewer than 256 rows; 2048 where the tiles alone fill the CUs): added to
+    // the gradient where it is formed
     // (gradient of 10 electrons, 2 walkers: 515 -> 501 us)
     if (S == 1) {
         hipLaunchKernelGGL((k_tn_partial<T, true>), grid, dim3(256), 0, st, X, ldx, NA, Y, ldy, NB, R, per, stride, off, rps, 1,
@@ -1095,7 +1093,7 @@ void launch_colsum(const T *in, int64_t ld, int C, int64_t R, T *part, double *a
     hipLaunchKernelGGL(k_colsum_reduce<T>, dim3(gridn(C)), dim3(256), 0, st, part, S, C, acc, off, env_map, off2);
 }
 
-int max_splits() { return 64; }
+int max_splits() { return MAX_SPLITS; }
 
 void launch_zero_f64(double *p, int64_t n, hipStream_t st)
 {

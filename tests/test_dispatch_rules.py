@@ -1,0 +1,40 @@
+"""Dispatch rules that need only sizes (csrc/fn_rules.h), compiled with the host
+compiler and checked over their ranges."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2401_10287_amd", "csrc")
+
+
+def _run(tmp_path, body):
+    if shutil.which("g++") is None:
+        pytest.skip("g++ not available")
+    src, exe = tmp_path / "rules.cc", tmp_path / "rules"
+    src.write_text('#include <stdio.h>\n#include "fn_rules.h"\nusing namespace fn;\nint main()\n{\n%s\nreturn 0;\n}\n' % body)
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    return [[int(v) for v in line.split()] for line in subprocess.run([str(exe)], check=True, capture_output=True,
+                                                                      text=True).stdout.splitlines()]
+
+
+def test_weight_gradient_splits(tmp_path):
+    """A wave's FP32 sum (a quarter of a split's rows) runs over at most 512 rows, or,
+    where the 64 splits of the partial sums' buffer (32 for the product that forms two
+    weight blocks) do not reach, over no more than 1/64 of the rows, at every width."""
+    out = _run(tmp_path, """
+    const int rows[] = {1, 7, 255, 256, 300, 2048, 2049, 5000, 8192, 12345, 32768, 32769, 49152, 81920, 163840, 1000003};
+    const int widths[] = {32, 64, 256, 384, 512, 1024};
+    for (int R : rows)
+        for (int w : widths)
+            for (int tile = 32; tile <= 64; tile *= 2)
+                for (int two = 1; two <= 2; ++two) {
+                    const int n = (w + tile - 1) / tile, tiles = two * n * n;
+                    printf("%d %d %d\\n", R, tiles, (int)tn_product_splits(R, tiles, 64 / two));
+                }""")
+    assert len(out) == 16 * 24
+    for rows, tiles, splits in out:
+        assert 1 <= splits <= 64
+        wave = -(-(-(-rows // splits)) // 4)
+        assert wave <= max(512, -(-rows // 64)), (rows, tiles, splits)
