@@ -687,8 +687,7 @@ __global__ __launch_bounds__(256) void k_pair_backward_mfma(Sys s, const double 
 // i, so one load of each operand feeds V x V instructions of a 16 V x 16 V tile
 // per wave, four rows at a time, straight from memory (no LDS, no barriers),
 // TN_PF such steps requested ahead.  The four waves of a workgroup take
-// consecutive parts of the split's rows and are added in wave order; all tiles
-// of a split follow each other on one XCD, so its rows come from HBM once.
+// consecutive parts of the split's rows and are added in wave order.
 // A single split (ONE) is added to the gradient here.
 // (A workgroup per 64 x 64 tile with 64 rows staged in LDS per barrier: 12
 // electrons, 4096 walkers, the gradient's 18 products 855 -> 590 us; FP64, 2
@@ -718,8 +717,9 @@ __global__ __launch_bounds__(256) void k_tn_partial(const T *__restrict__ X, int
     __shared__ T sum[ONE ? W : 1][W + V];                                // the tile, where it goes straight to the gradient
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nta = (NA + W - 1) / W, tiles = nta * ((NB + W - 1) / W);
-    const int idx = (int)(blockIdx.x >> 3), sp = (idx / tiles) * 8 + (int)(blockIdx.x & 7), tile = idx % tiles;
-    if (sp >= S) return;
+    const TnBlock blk = tn_block((int)blockIdx.x, S, tiles);
+    const int sp = blk.sp, tile = blk.tile;
+    if (sp >= S || tile >= tiles) return;
     const int a0 = (tile % nta) * W, b0 = (tile / nta) * W;
     const int64_t s0 = (int64_t)sp * rows_per_split, s1 = s0 + rows_per_split < R ? s0 + rows_per_split : R;
     const int64_t rw = (rows_per_split + 3) / 4;               // rows of a wave
@@ -1066,7 +1066,7 @@ void launch_tn(const T *X, int64_t ldx, int NA, const T *Y, int64_t ldy, int NB,
     const int tiles = ((NA + W - 1) / W) * ((NB + W - 1) / W);
     const int64_t S = tn_product_splits(R, tiles, part_elems / ((int64_t)NA * NB));
     const int64_t rps = (R + S - 1) / S;
-    const dim3 grid((unsigned)((S + 7) / 8 * 8 * tiles));
+    const dim3 grid((unsigned)tn_grid((int)S, tiles));
     // one split (fewer than 256 rows; 2048 where the tiles alone fill the CUs): added to
     // the gradient where it is formed
     // (gradient of 10 electrons, 2 walkers: 515 -> 501 us)

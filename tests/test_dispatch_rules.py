@@ -38,3 +38,24 @@ def test_weight_gradient_splits(tmp_path):
         assert 1 <= splits <= 64
         wave = -(-(-(-rows // splits)) // 4)
         assert wave <= max(512, -(-rows // 64)), (rows, tiles, splits)
+
+
+def test_weight_gradient_workgroups(tmp_path):
+    """Every (split, tile) has one workgroup, and of the eight XCDs, to which workgroups
+    are dealt in turn, none has more than 1.8 times its share (nine splits: two on one)."""
+    out = _run(tmp_path, """
+    const int tiles[] = {1, 3, 16, 32, 256, 512};
+    const int splits[] = {1, 2, 3, 4, 5, 7, 8, 9, 13, 16, 25, 64};
+    for (int t : tiles)
+        for (int S : splits)
+            for (int b = 0; b < tn_grid(S, t); ++b)
+                printf("%d %d %d %d %d\\n", t, S, b % 8, tn_block(b, S, t).sp, tn_block(b, S, t).tile);""")
+    cases = {}
+    for t, s, xcd, sp, tile in out:
+        if sp < s and tile < t:
+            cases.setdefault((t, s), []).append((xcd, sp, tile))
+    assert len(cases) == 72
+    for (t, s), work in cases.items():
+        assert sorted(w[1:] for w in work) == [(sp, tile) for sp in range(s) for tile in range(t)]
+        per = [sum(w[0] == x for w in work) for x in range(8)]
+        assert max(per) <= 1.8 * s * t / 8 + 1, (t, s, per)
