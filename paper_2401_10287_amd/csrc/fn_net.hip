@@ -1065,6 +1065,9 @@ __host__ __device__ inline size_t orbdet_stage_off(int n, bool fl)
 // (forward-Laplacian form, spins of up to ORB_PF electrons).  Spins that the
 // direction-per-lane kernel of fn_det.hip does not take: 11 to 16 electrons.
 // Spins sp0 .. sp0 + nsp - 1 of equal size, B * K workgroups each.
+// (The size tests that REG decides already keep the compiler at 126 registers and four
+// waves per SIMD in FP32; without them 143 and three: local energies of 8 electrons of one
+// spin, 4096 walkers 1.50 ms where this form takes 1.32, 12 and 12, 64 walkers 332 us and 324.)
 template <typename T, bool FL, bool REG, bool ST>
 __global__ __launch_bounds__(64) void k_orbdet(Sys s, const double *x, const T *theta, OrbSpins<T> S, int sp0,
                                                int64_t B, int TR, double *DR, int rec)
@@ -1179,7 +1182,7 @@ __global__ __launch_bounds__(64) void k_orbdet(Sys s, const double *x, const T *
             const int mt = t0 + d, j = j0 + jj;
             const T *Oj = O + ((w * n + jj) * TR) * ldo + k * n;
             double *v = Mc + d * nn;
-            if constexpr (REG) {
+            if (n <= ORB_PF) {
                 // every row's head value is requested before the first is used
                 // (the stores below would otherwise order each load after the
                 // previous row's store)
@@ -1191,8 +1194,9 @@ __global__ __launch_bounds__(64) void k_orbdet(Sys s, const double *x, const T *
                 for (int r = 0; r < ORB_PF; ++r) pv[r] = perm[r < n ? r : n - 1];
 #pragma unroll
                 for (int r = 0; r < ORB_PF; ++r) ov[r] = (double)Oj[orow * ldo + pv[r]];
-                // right-hand side and both triangular solves in registers
-                // (static indices), the solved column stored once
+                // REG: right-hand side and both triangular solves in registers
+                // (static indices), the solved column stored once; otherwise
+                // the right-hand side goes to LDS for the solves below
                 double vv[ORB_PF];
 #pragma unroll
                 for (int r = 0; r < ORB_PF; ++r) {
@@ -1208,9 +1212,11 @@ __global__ __launch_bounds__(64) void k_orbdet(Sys s, const double *x, const T *
                             for (int a = 0; a < 3; ++a)
                                 dv += 2.0 * (double)Oj[(1 + 3 * j + a) * ldo + io] * GE[3 * e + a];
                         }
-                        vv[r] = dv;
+                        if constexpr (REG) vv[r] = dv;
+                        else v[r * n + jj] = dv;
                     }
                 }
+                if constexpr (REG) {
 #pragma unroll
                 for (int r = 1; r < ORB_PF; ++r) {
                     if (r < n) {
@@ -1233,6 +1239,7 @@ __global__ __launch_bounds__(64) void k_orbdet(Sys s, const double *x, const T *
 #pragma unroll
                 for (int r = 0; r < ORB_PF; ++r)
                     if (r < n) v[r * n + jj] = vv[r];
+                }
             } else {
                 for (int r = 0; r < n; ++r) {
                     const int io = perm[r], e = io * n + jj;
@@ -1246,6 +1253,8 @@ __global__ __launch_bounds__(64) void k_orbdet(Sys s, const double *x, const T *
                     }
                     v[r * n + jj] = dv;
                 }
+            }
+            if (!REG || n > ORB_PF) {
                 for (int r = 1; r < n; ++r) {
                     double acc = v[r * n + jj];
                     for (int c = 0; c < r; ++c) acc -= LU[r * n + c] * v[c * n + jj];
