@@ -29,6 +29,7 @@
 #include "fn_env.h"
 #include "fn_internal.h"
 #include "fn_kernels.h"
+#include "fn_rules.h"
 
 namespace fn {
 
@@ -329,6 +330,7 @@ bool launch_orbdet_lanes(const Sys &s, const double *x, const T *theta, const Or
 {
     if (B * s.K * nsp > (int64_t)1 << 31) return false;
     if (fl) {
+        if (!det_lanes_fl(n, s.N, s.M, sizeof(T) == 8)) return false;
         switch (n) {
 #define FN_LANES(NS)                                                                              \
     case NS: launch_lanes<T, NS, true>(s, x, theta, S, sp0, nsp, B, TR, DR, rec, st); return true;

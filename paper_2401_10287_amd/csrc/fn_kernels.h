@@ -77,8 +77,8 @@ template <typename T>
 void launch_orbdet(const Sys &s, const double *x, const T *theta, const OrbSpins<T> &S, int64_t B, int TR, bool fl,
                    double *DR, int rec, hipStream_t st);
 // One wave per determinant with a direction per lane (fn_det.hip), spins of 3
-// to 10 electrons in forward-Laplacian form, 9 and 10 for the value alone;
-// false (nothing launched) for other sizes.
+// to 10 electrons in forward-Laplacian form (det_lanes_fl in fn_rules.h), 9 and
+// 10 for the value alone; false (nothing launched) for other sizes.
 template <typename T>
 bool launch_orbdet_lanes(const Sys &s, const double *x, const T *theta, const OrbSpins<T> &S, int sp0, int nsp, int n,
                          int64_t B, int TR, bool fl, double *DR, int rec, hipStream_t st);

@@ -1063,7 +1063,8 @@ __host__ __device__ inline size_t orbdet_stage_off(int n, bool fl)
 // FL = false: value only (envelope, LU, sign and log|det|), LDS holds the matrix only.
 // REG: right-hand sides and triangular solves of the directions in registers
 // (forward-Laplacian form, spins of up to ORB_PF electrons).  Spins that the
-// direction-per-lane kernel of fn_det.hip does not take: 11 to 16 electrons.
+// direction-per-lane kernel of fn_det.hip does not take: 11 to 16 electrons,
+// and 8 to 10 in FP32 with few electrons in all (det_lanes_fl in fn_rules.h).
 // Spins sp0 .. sp0 + nsp - 1 of equal size, B * K workgroups each.
 // (The size tests that REG decides already keep the compiler at 126 registers and four
 // waves per SIMD in FP32; without them 143 and three: local energies of 8 electrons of one

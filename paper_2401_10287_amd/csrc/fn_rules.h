@@ -47,4 +47,20 @@ constexpr int64_t tn_grid(int S, int tiles)
     return tn_xcds(S) > 1 ? 8 * ceil_div(tiles, tn_xcds(S)) : 8 * ceil_div(S, 8) * tiles;
 }
 
+// Forward-Laplacian determinants of n electrons of one spin (N in all, M nuclei) in
+// the direction-per-lane kernel (else a wave per determinant with the matrices in
+// LDS).  A lane per direction takes the same time for 20 electrons as for 8, the other
+// kernel less for fewer, and its entries are formed at a higher occupancy; the line
+// does not depend on the batch, so that the bits do not.  FP32, 16 determinants, 4096
+// walkers, wave per determinant / here, us per local energy of a small network: (8, 0)
+// and 2 nuclei 1321 / 1343, 20 nuclei 1770 / 2013; (8, 3) 20 nuclei 3449 / 3342; (9, 0)
+// 1775 / 1967; (9, 2) 2445 / 2523; (9, 3) 2895 / 2725, 20 nuclei 4379 / 4453; (10, 0) 2299 /
+// 2156, 20 nuclei 3071 / 3265; (10, 2) 20 nuclei 4355 / 4309.  Seven or fewer gain
+// 1.06x or more at 32 nuclei, FP64 1.2x at any size.
+constexpr bool det_lanes_fl(int n, int N, int M, bool f64)
+{
+    if (n < 3 || n > 10) return false;
+    return f64 || n < 8 || N > (n == 9 ? 11 : 9) + M / 8;
+}
+
 }  // namespace fn

@@ -59,3 +59,14 @@ def test_weight_gradient_workgroups(tmp_path):
         assert sorted(w[1:] for w in work) == [(sp, tile) for sp in range(s) for tile in range(t)]
         per = [sum(w[0] == x for w in work) for x in range(8)]
         assert max(per) <= 1.8 * s * t / 8 + 1, (t, s, per)
+
+
+def test_determinant_kernel_choice(tmp_path):
+    """The direction-per-lane kernel where it was measured to be the faster one, the wave
+    per determinant elsewhere: (electrons of the spin, of both, nuclei, FP64, lanes)."""
+    cases = [(2, 4, 1, 0, 0), (3, 3, 32, 0, 1), (7, 7, 32, 0, 1), (8, 8, 2, 0, 0), (8, 10, 20, 0, 0), (8, 10, 1, 0, 1),
+             (8, 15, 20, 0, 1), (9, 9, 1, 0, 0), (9, 11, 2, 0, 0), (9, 12, 2, 0, 1), (9, 12, 20, 0, 0), (9, 18, 20, 0, 1),
+             (10, 10, 2, 0, 1), (10, 10, 20, 0, 0), (10, 12, 32, 0, 0), (10, 20, 20, 0, 1), (11, 20, 2, 0, 0),
+             (8, 8, 20, 1, 1), (10, 10, 32, 1, 1), (11, 11, 2, 1, 0)]
+    out = _run(tmp_path, "\n".join('printf("%%d\\n", (int)det_lanes_fl(%d, %d, %d, %d));' % c[:4] for c in cases))
+    assert [v[0] for v in out] == [c[4] for c in cases]
