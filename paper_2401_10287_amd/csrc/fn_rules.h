@@ -47,6 +47,27 @@ constexpr int64_t tn_grid(int S, int tiles)
     return tn_xcds(S) > 1 ? 8 * ceil_div(tiles, tn_xcds(S)) : 8 * ceil_div(S, 8) * tiles;
 }
 
+// Batches for which a stream layer walks over whole walkers (fn_walk.hip): it takes a
+// round of `slots` walkers at a time, the tiled kernel spreads any number of rows, so
+// the last round has to be full enough.  live: 16-row blocks of an electron; six: six
+// products (else BF16 weights, three).  Whole local energies, tiled -> walking (us):
+// 12 electrons, BF16 weights, 128 walkers (half a round) 501 -> 487, 257 914 -> 903, 300
+// 1039 -> 930, 512 1681 -> 1224, but 100 427 -> 452; 20 electrons, 200 1836 -> 1632.
+// 10 electrons (two blocks, where the epilogue weighs more) 256 535 -> 476, 1024 1871 ->
+// 1556, but 300 619 -> 659; with six products it gains nothing there (7 electrons, 1024
+// walkers: 1346 -> 1393) and is not used.  Six products otherwise, slots 128, times
+// faster: 11 to 15 electrons 72 walkers 0.97 to 1.07, 82 1.01 to 1.09, 128 1.29 to 1.35, 143
+// 1.07 to 1.09; 16 to 20 electrons 72 0.89 to 1.01, 82 0.95 to 1.11, 92 1.00 to 1.12, 128 1.14 to
+// 1.25, 143 0.96 to 1.06, 154 1.01 to 1.15.
+constexpr bool walk_batch(int64_t B, int64_t slots, int live, bool six)
+{
+    const int64_t rounds = ceil_div(B, slots);
+    int full = live >= 3 ? 55 : 85;                  // percent of the rounds' walkers
+    if (six && live == 3 && rounds == 1) full = 60;
+    if (six && live == 4) full = rounds == 1 ? 70 : 58;
+    return !(six && live < 3) && 100 * B >= full * rounds * slots;
+}
+
 // Forward-Laplacian determinants of n electrons of one spin (N in all, M nuclei) in
 // the direction-per-lane kernel (else a wave per determinant with the matrices in
 // LDS).  A lane per direction takes the same time for 20 electrons as for 8, the other

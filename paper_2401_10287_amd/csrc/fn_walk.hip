@@ -27,6 +27,7 @@
 // 4096 walkers 9.5 -> 5.6 ms; 20 electrons, 8192 walkers 41.8 -> 26.6 ms.
 #include "fn_internal.h"
 #include "fn_kernels.h"
+#include "fn_rules.h"
 
 namespace fn {
 
@@ -503,24 +504,15 @@ static int walk_slots(int mode) { return mode == GEMM_BF16W3 ? 512 / WalkShape<G
 // Shapes: 32 or 64 rows per electron, widths 256, a row's inputs in 2, 4 or 10
 // steps of 32 (the features of up to 8 or of 17..24 nuclei with 4-wide pair
 // rows; 256-wide layers with 32-wide pairs).
-// Batches: the kernel takes a round of `slots` walkers at a time, the tiled one
-// spreads any number of rows, so the last round has to be full enough.  Whole
-// local energies, tiled -> walking (us): 12 electrons, BF16 weights, 128
-// walkers (half a round) 501 -> 487, 257 914 -> 903, 300 1039 -> 930, 512 1681
-// -> 1224, but 100 427 -> 452; 20 electrons, 200 1836 -> 1632; 12 electrons,
-// six products, 256 1006 -> 882.  With 32 rows per electron the epilogue
-// weighs more: 10 electrons, BF16 weights, 256 535 -> 476, 1024 1871 -> 1556,
-// but 300 619 -> 659; with six products it gains nothing (7 electrons, 1024
-// walkers: 1346 -> 1393) and is not used.
+// Batches: walk_batch in fn_rules.h.
 bool walk_layer_supported(int mode, const LayerArgs &a, int TR, int64_t B)
 {
     const int ks = (a.K1 + a.K2) / 32, live = (a.n3 + 2 + 15) / 16;
-    if (!(mode == GEMM_BF16W3 || (mode == GEMM_BF16X6 && live >= 3)) || (TR != 32 && TR != 64) || a.w1 != 256 ||
+    if (!(mode == GEMM_BF16W3 || mode == GEMM_BF16X6) || (TR != 32 && TR != 64) || a.w1 != 256 ||
         a.W1p != 256 || a.lda1 != 256 || a.ldh_out != 256 || a.nout != 256 || a.resid != (ks == 10) ||
         !(ks == 10 ? a.K1 == 256 : (ks == 2 || ks == 4) && a.K2 == 32))
         return false;
-    const int64_t slots = walk_slots(mode), rounds = (B + slots - 1) / slots;
-    return 100 * B >= (live >= 3 ? 55 : 85) * rounds * slots;
+    return walk_batch(B, walk_slots(mode), live, mode == GEMM_BF16X6);
 }
 
 template <int MODE, int LIVE, int KS>

@@ -70,3 +70,14 @@ def test_determinant_kernel_choice(tmp_path):
              (8, 8, 20, 1, 1), (10, 10, 32, 1, 1), (11, 11, 2, 1, 0)]
     out = _run(tmp_path, "\n".join('printf("%%d\\n", (int)det_lanes_fl(%d, %d, %d, %d));' % c[:4] for c in cases))
     assert [v[0] for v in out] == [c[4] for c in cases]
+
+
+def test_walking_layer_batches(tmp_path):
+    """The walking stream layer only for batches where it was measured to be the faster
+    one: (walkers, walkers of a round, 16-row blocks of an electron, six products, walks)."""
+    cases = [(141, 256, 3, 0, 1), (140, 256, 3, 0, 0), (300, 256, 3, 0, 1), (218, 256, 2, 0, 1), (217, 256, 2, 0, 0),
+             (300, 256, 2, 0, 0), (4096, 256, 4, 0, 1), (72, 128, 3, 1, 0), (82, 128, 3, 1, 1), (143, 128, 3, 1, 1),
+             (72, 128, 4, 1, 0), (85, 128, 4, 1, 0), (92, 128, 4, 1, 1), (128, 128, 4, 1, 1), (143, 128, 4, 1, 0),
+             (154, 128, 4, 1, 1), (1000, 128, 4, 1, 1), (1024, 128, 2, 1, 0)]
+    out = _run(tmp_path, "\n".join('printf("%%d\\n", (int)walk_batch(%d, %d, %d, %d));' % c[:4] for c in cases))
+    assert [v[0] for v in out] == [c[4] for c in cases]
