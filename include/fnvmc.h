@@ -368,7 +368,9 @@ const char *fn_server_last_error(void);
    product), "head_gemm", "features", "pair_stream", "spin_mean",
    "layer_epilogue", "envelope", "det", "combine", "pack", "propose",
    "accept" (counts no launches: the acceptance runs in the "combine"
-   kernel of the proposal), "backward".  Not thread-safe with concurrent
+   kernel of the proposal), "backward", "small_net" (log|psi| or a whole call's
+   moves of a small FP64 network in one launch; no other class counts then).
+   Not thread-safe with concurrent
    library calls.
    fn_timing_select(name) restricts the brackets to that one class (each
    pair of event records adds a few microseconds to the stream), NULL

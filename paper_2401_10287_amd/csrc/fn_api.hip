@@ -39,10 +39,10 @@ fn_status fail(fn_status st, const std::string &msg)
 // per-kernel timing (diagnostics)
 // ---------------------------------------------------------------------------
 enum KClass { K_STREAM_GEMM, K_WALKER_GEMM, K_HEAD_GEMM, K_FEATURES, K_PAIR, K_SPIN_MEAN, K_EPI, K_ENV, K_DET,
-              K_COMBINE, K_PACK, K_PROPOSE, K_ACCEPT, K_BACKWARD, K_NCLASS };
+              K_COMBINE, K_PACK, K_PROPOSE, K_ACCEPT, K_BACKWARD, K_SMALL, K_NCLASS };
 const char *const kclass_names[K_NCLASS] = {"stream_gemm", "walker_gemm", "head_gemm", "features", "pair_stream",
                                            "spin_mean", "layer_epilogue", "envelope", "det", "combine", "pack",
-                                           "propose", "accept", "backward"};
+                                           "propose", "accept", "backward", "small_net"};
 struct TimeRec { int cls; hipEvent_t a, b; };
 std::mutex g_tmu;
 bool g_timing = false;
@@ -766,7 +766,7 @@ fn_status run_forward(const Ctx &c, const Plan &p, const void *theta, const doub
 {
     if constexpr (std::is_same<T, double>::value)
         if (!e_loc && small_walk_supported(c.s, c.P, B)) {
-            Timed t_(K_STREAM_GEMM, st);
+            Timed t_(K_SMALL, st);
             launch_small_walk(c.s, c.P, (const double *)theta, const_cast<double *>(x), log_abs, sign, B, 0, 0.0,
                               GroupTable{}, nullptr, nullptr, nullptr, st);
             return hip_status();
@@ -792,7 +792,7 @@ fn_status run_metropolis(const Ctx &c, const Plan &p, const void *theta, double 
             g.k1[0] = (uint32_t)(seed >> 32);
             g.step[0] = (uint32_t)step0;
             g.stream[0] = stream_id;
-            Timed t_(K_STREAM_GEMM, st);
+            Timed t_(K_SMALL, st);
             launch_small_walk(c.s, c.P, (const double *)theta, x, log_abs, nullptr, B, n_steps, sigma, g, z, u, n_accept, st);
             return hip_status();
         }
@@ -832,7 +832,7 @@ fn_status run_metropolis_group(const Ctx &c, const Plan &p, const void *theta, d
     if constexpr (std::is_same<T, double>::value)
         if (small_walk_supported(c.s, c.P, B)) {
             for (int q = 0; q < n_jobs; ++q) g.step[q] = (uint32_t)jobs[q].step0;
-            Timed t_(K_STREAM_GEMM, st);
+            Timed t_(K_SMALL, st);
             launch_small_walk(c.s, c.P, (const double *)theta, x, log_abs, nullptr, B, n_steps, sigma, g, nullptr, nullptr,
                               n_accept, st);
             return hip_status();

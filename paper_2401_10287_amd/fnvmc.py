@@ -100,7 +100,7 @@ EXPORTED = ["fn_param_count", "fn_workspace_bytes", "fn_log_psi", "fn_local_ener
             "fn_server_step", "fn_server_result", "fn_server_cancel", "fn_server_memory", "fn_server_destroy",
             "fn_server_last_error"]
 KERNEL_CLASSES = ["stream_gemm", "walker_gemm", "head_gemm", "features", "pair_stream", "spin_mean", "layer_epilogue",
-                  "envelope", "det", "combine", "pack", "propose", "accept", "backward"]
+                  "envelope", "det", "combine", "pack", "propose", "accept", "backward", "small_net"]
 
 
 def _check(status: int):
