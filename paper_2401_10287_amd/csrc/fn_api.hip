@@ -492,8 +492,10 @@ void forward_chunk(const Ctx &c, const Plan &p, const T *theta, const double *xw
         ga.A1 = G; ga.lda1 = 2 * HWl; ga.K1 = 2 * HWl;
         ga.W = ws + p.wg[l]; ga.wpart = p.wgpart[l]; ga.ldw = 2 * HWl;
         ga.C = Pw; ga.ldc = s.w1;
-        // rows value .. Laplacian of each walker only: both epilogues read
-        // no padding row of the per-walker part
+        // rows value .. Laplacian of each walker only: no epilogue uses a padding
+        // row of the per-walker part.  (The walking kernel loads the padding rows of
+        // Pw and of h up to a multiple of 16, which nothing has written: they have to be
+        // allocated, TR rows each, and its results do not depend on them.)
         const int tr_live = fl ? n3 + 2 : TR;
         ga.rows = b * tr_live; ga.nout = s.w1;
         ga.rows_per_group = tr_live; ga.group_stride = TR;

@@ -176,7 +176,10 @@ __global__ __launch_bounds__(64 * WALK_WAVES, 2) void k_walk_layer(LayerArgs a, 
     lds_barrier();
     int cur = 0;
     for (int64_t w = blk; w < B; w += nblk) {
-        f32x4 pp[LIVE][WJ];                            // the per-walker part
+        // the per-walker part; here and for the residual's rows, rows past the Laplacian
+        // row (tl) hold whatever memory held: they stay in their own lane's rows, are masked
+        // out of the Laplacian's source and never stored
+        f32x4 pp[LIVE][WJ];
 #pragma unroll
         for (int i = 0; i < LIVE; ++i)
 #pragma unroll
