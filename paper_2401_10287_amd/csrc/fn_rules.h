@@ -28,23 +28,28 @@ constexpr int64_t tn_product_splits(int64_t R, int64_t tiles, int64_t cap)
 
 // The split and output tile of workgroup `bid`.  Workgroups are dealt to the eight
 // XCDs in turn; all tiles of a split follow each other on one XCD, so its rows come
-// from HBM once.  Up to four splits would leave half of the XCDs or more idle: a split's
-// tiles then go to 8, 4 or 2 of them.  (sp >= S or tile >= tiles: no work.)  Gradients,
-// 1024 wide: 2 electrons, 16 walkers (one split) 913 us with its tiles on one XCD, 753
-// on eight; 12 electrons, 1024 walkers (six, and two for the means) 3785 -> 3205.
+// from HBM once.  Up to four splits of more tiles than an XCD has CUs would leave half of
+// the XCDs or more idle: a split's tiles then go to 8, 4 or 2 of them.  (sp >= S or
+// tile >= tiles: no work.)  Gradients, 1024 wide: 2 electrons, 16 walkers (one split) 913
+// us with its tiles on one XCD, 753 on eight; 12 electrons, 1024 walkers (six, and two for
+// the means) 3785 -> 3205.
 struct TnBlock {
     int sp, tile;
 };
-constexpr int tn_xcds(int S) { return S == 1 ? 8 : (S == 2 ? 4 : (S <= 4 ? 2 : 1)); }
+constexpr int tn_xcd_bits(int S, int tiles)
+{
+    return tiles <= 32 || S > 4 ? 0 : (S == 1 ? 3 : (S == 2 ? 2 : 1));
+}
 constexpr TnBlock tn_block(int bid, int S, int tiles)
 {
-    const int g = tn_xcds(S), xcd = bid % 8, idx = bid / 8;
-    if (g > 1) return TnBlock{xcd / g, idx * g + xcd % g};
+    const int b = tn_xcd_bits(S, tiles), xcd = bid & 7, idx = bid >> 3;
+    if (b > 0) return TnBlock{xcd >> b, (idx << b) + (xcd & ((1 << b) - 1))};
     return TnBlock{(idx / tiles) * 8 + xcd, idx % tiles};
 }
 constexpr int64_t tn_grid(int S, int tiles)
 {
-    return tn_xcds(S) > 1 ? 8 * ceil_div(tiles, tn_xcds(S)) : 8 * ceil_div(S, 8) * tiles;
+    const int b = tn_xcd_bits(S, tiles);
+    return b > 0 ? 8 * ceil_div(tiles, 1 << b) : 8 * ceil_div(S, 8) * tiles;
 }
 
 // Batches for which a stream layer walks over whole walkers (fn_walk.hip): it takes a
