@@ -193,9 +193,10 @@ fn_status sfail(fn_status st, const std::string &m)
     return st;
 }
 
-// the small-batch split-reduction products change the summation order with
-// the batch size; every server call runs without them, so a job's results do
-// not depend on which gang it runs in
+// the small-batch split-reduction products and the batch limit of the small FP64
+// networks' one launch change the summation order with the batch size; every
+// server call runs without them, so a job's results do not depend on which
+// gang it runs in
 struct NoSplitK {
     bool prev = fn::g_splitk_suppressed;
     NoSplitK() { fn::g_splitk_suppressed = true; }
